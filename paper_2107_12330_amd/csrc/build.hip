@@ -81,10 +81,11 @@ __device__ __forceinline__ uint32_t graph_of_edge(const BatchMap &bm, size_t i)
 // and then only steps forward through the edge offsets.
 // dbit = 1 (directed inputs) appends the direction of the raw edge to its
 // key: 0 for lower id -> higher id, 1 for the reverse.
-__global__ void k_canon(const uint32_t *src, const uint32_t *dst, const uint32_t *ts, size_t M, uint32_t n,
+__global__ __launch_bounds__(kB) void k_canon(const uint32_t *src, const uint32_t *dst, const uint32_t *ts, size_t M, uint32_t n,
                         PairCode pc, int dbit, uint64_t sentinel, uint64_t *keys, uint32_t *vals,
                         unsigned long long *bad, unsigned long long *loops, BatchMap bm, size_t per_block)
 {
+    __shared__ unsigned long long tmp[kB / kWave];
     unsigned long long nbad = 0, nloop = 0;
     const size_t begin = blockIdx.x * per_block;
     const size_t end = begin + per_block < M ? begin + per_block : M;
@@ -122,12 +123,8 @@ __global__ void k_canon(const uint32_t *src, const uint32_t *dst, const uint32_t
         keys[i] = k;
         vals[i] = ts ? ts[i] : 0u;
     }
-    nbad = wave_sum(nbad);
-    nloop = wave_sum(nloop);
-    if (lane_id() == 0) {
-        if (nbad) atomicAdd(bad, nbad);
-        if (nloop) atomicAdd(loops, nloop);
-    }
+    block_add<kB>(nbad, tmp, bad);
+    block_add<kB>(nloop, tmp, loops);
 }
 
 // ------------------------------------------------------------ phase 2
@@ -300,13 +297,13 @@ __global__ void k_degree_runs(const uint32_t *v, size_t m, uint32_t *deg)
 }
 
 template <class T>
-__global__ void k_max(const T *x, size_t n, unsigned long long *out)
+__global__ __launch_bounds__(kB) void k_max(const T *x, size_t n, unsigned long long *out)
 {
+    __shared__ unsigned long long tmp[kB / kWave];
     unsigned long long mx = 0;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         mx = max(mx, (unsigned long long)x[i]);
-    mx = wave_max(mx);
-    if (lane_id() == 0 && mx) atomicMax(out, mx);
+    block_max<kB>(mx, tmp, out);
 }
 
 // A bijection of [0, 2^nb): xor-shifts and odd multiplications modulo 2^nb.
@@ -466,21 +463,20 @@ __global__ void k_csr(const uint64_t *okey, size_t m, PairCode pc, const uint8_t
     }
 }
 
-__global__ void k_row_stats(const uint64_t *rowptr, uint32_t n, unsigned long long *wedges,
-                            unsigned long long *dplus_max)
+// (One atomic per block and value: with one per wave the scale-22 graph's
+// pass took 780 us, nearly all of it the atomics.)
+__global__ __launch_bounds__(kB) void k_row_stats(const uint64_t *rowptr, uint32_t n, unsigned long long *wedges,
+                                                  unsigned long long *dplus_max)
 {
+    __shared__ unsigned long long tmp[kB / kWave];
     unsigned long long w = 0, mx = 0;
     for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < n; v += (size_t)gridDim.x * blockDim.x) {
         const uint64_t d = rowptr[v + 1] - rowptr[v];
         w += d ? d * (d - 1) / 2 : 0;
         mx = max(mx, (unsigned long long)d);
     }
-    w = wave_sum(w);
-    mx = wave_max(mx);
-    if (lane_id() == 0) {
-        if (w) atomicAdd(wedges, w);
-        if (mx) atomicMax(dplus_max, mx);
-    }
+    block_add<kB>(w, tmp, wedges);
+    block_max<kB>(mx, tmp, dplus_max);
 }
 
 // ------------------------------------------------------------ phase 6
@@ -512,10 +508,12 @@ __global__ void k_has_out(const uint64_t *rowptr, uint32_t n, uint64_t *bits)
 // length of the rest of p's row after slot k (< 2^22) | label(p) << 24.
 // Counts the edges kept.  Slots are in row order, so every read here walks
 // memory forwards, but for the bit of q.
-__global__ void k_in_keys(const uint32_t *srow, const uint32_t *col, const uint64_t *rowptr, const uint64_t *has_out,
+// (The count leaves with one atomic per block, as in k_row_stats.)
+__global__ __launch_bounds__(kB) void k_in_keys(const uint32_t *srow, const uint32_t *col, const uint64_t *rowptr, const uint64_t *has_out,
                           const uint8_t *rlab, size_t m, int kbits, uint32_t n, uint64_t *key, uint32_t *pay,
                           unsigned long long *kept)
 {
+    __shared__ unsigned long long tmp[kB / kWave];
     unsigned long long c = 0;
     for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < m; k += (size_t)gridDim.x * blockDim.x) {
         const uint32_t s = srow[k], t = col[k];
@@ -525,8 +523,7 @@ __global__ void k_in_keys(const uint32_t *srow, const uint32_t *col, const uint6
         pay[k] = rest | ((uint32_t)rlab[s] << 24);
         c += ok ? 1 : 0;
     }
-    c = wave_sum(c);
-    if (lane_id() == 0 && c) atomicAdd(kept, c);
+    block_add<kB>(c, tmp, kept);
 }
 
 // In-edges and wedge checks of every target (the sum of the remaining row
@@ -1094,10 +1091,10 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
             k_degree_runs<<<grid_for(m, kB), kB, 0, s>>>(hb2 ? hiB : hiA, m, deg.get());
             TP_CHECK_LAUNCH();
         }
-        k_max<uint32_t><<<grid_for(n, kB), kB, 0, s>>>(deg.get(), n, c_dmax);
+        k_max<uint32_t><<<grid_for(n, kB, kStatBlocks), kB, 0, s>>>(deg.get(), n, c_dmax);
         TP_CHECK_LAUNCH();
         if (vlab) {
-            k_max<uint8_t><<<grid_for(n, kB), kB, 0, s>>>(vlab, n, c_lab);
+            k_max<uint8_t><<<grid_for(n, kB, kStatBlocks), kB, 0, s>>>(vlab, n, c_lab);
             TP_CHECK_LAUNCH();
         }
         unsigned long long mx[2];
@@ -1182,7 +1179,7 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
     g->rowptr.reset((size_t)n + 1, s);
     scan_u32_to_u64(dplus.get(), g->rowptr.get(), n, s);
     dplus.release();
-    k_row_stats<<<grid_for(n, kB), kB, 0, s>>>(g->rowptr.get(), n, c_wedge, c_dpmax);
+    k_row_stats<<<grid_for(n, kB, kStatBlocks), kB, 0, s>>>(g->rowptr.get(), n, c_wedge, c_dpmax);
     TP_CHECK_LAUNCH();
     if (g->dbin_rank.get()) {
         const size_t nbins = g->dbin_rank.n;
@@ -1209,7 +1206,7 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
             has_out.reset((n + 63) / 64, s);
             k_has_out<<<grid_for(n, kB), kB, 0, s>>>(g->rowptr.get(), n, has_out.get());
             TP_CHECK_LAUNCH();
-            k_in_keys<<<grid_for(m, kB), kB, 0, s>>>(srow, g->col.get(), g->rowptr.get(), has_out.get(),
+            k_in_keys<<<grid_for(m, kB, kStatBlocks), kB, 0, s>>>(srow, g->col.get(), g->rowptr.get(), has_out.get(),
                                                      g->rlab.get(), m, kbits, n, ikey, ival, kept.get());
             TP_CHECK_LAUNCH();
         }

@@ -211,6 +211,40 @@ __device__ __forceinline__ T block_excl_scan(T v, T *tmp, T &total)
     return base + incl - v;
 }
 
+// Add the block's sum of v to *out, one atomic per block (none for 0); `tmp`
+// is LDS of BLOCK/64 words.  A wave's atomic each serialises: 65,536 of them
+// on one address take about 0.75 ms.
+template <int BLOCK>
+__device__ __forceinline__ void block_add(unsigned long long v, unsigned long long *tmp, unsigned long long *out)
+{
+    v = wave_sum(v);
+    if (lane_id() == 0) tmp[threadIdx.x / kWave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < BLOCK / kWave; ++w) v += tmp[w];
+        if (v) atomicAdd(out, v);
+    }
+    __syncthreads();
+}
+
+// The same for the largest v of the block.
+template <int BLOCK>
+__device__ __forceinline__ void block_max(unsigned long long v, unsigned long long *tmp, unsigned long long *out)
+{
+    v = wave_max(v);
+    if (lane_id() == 0) tmp[threadIdx.x / kWave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < BLOCK / kWave; ++w) v = v > tmp[w] ? v : tmp[w];
+        if (v) atomicMax(out, v);
+    }
+    __syncthreads();
+}
+
+// Blocks of a pass that ends in such an atomic: enough to fill the device
+// (8 a compute unit), few enough that the atomics take some 20 us.
+constexpr unsigned kStatBlocks = 2048;
+
 // ---------------------------------------------------------------- primitives (prim.hip)
 
 // Exclusive scan of n uint64 values (in may equal out).  Returns nothing; the
