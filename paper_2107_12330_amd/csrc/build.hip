@@ -583,6 +583,23 @@ __device__ __forceinline__ uint32_t tiles_of(uint64_t cnt, uint64_t work, uint32
     return (uint32_t)t;
 }
 
+// The caps of the work tiles (the cut the surveys walk): where a class has
+// too little work to give every claimer of a full device about
+// kShare tiles at the plan's cap, its records are cut finer, down to a floor
+// below which a tile's table and claim would outweigh its records.  The
+// claimers are waves for the tiny class and workgroups for the others, as
+// many as 256 compute units hold (32 waves, 5 and 1 workgroups each).  Without
+// it a small graph waits for the one wave or workgroup that walks its largest
+// target (scale 13: 1024 records on one wave, 247 us of a 380 us survey).
+__device__ __forceinline__ uint32_t work_rec_cap(int c, uint32_t rec_cap, uint64_t class_records)
+{
+    constexpr uint64_t kShare = 4;
+    const uint64_t claimers = c == kClassTiny ? 256 * 32 : (c == kClassSmall ? 256 * 5 : 256);
+    const uint32_t least = c == kClassTiny || c == kClassSmall ? kWorkRecMin : kWorkRecMinLarge;
+    const uint64_t want = class_records / (claimers * kShare);
+    return (uint32_t)min((uint64_t)rec_cap, max((uint64_t)least, want));
+}
+
 // Records of piece j of target q (pieces of huge targets; pos[] is the
 // exclusive scan of the cut flags, fbase[] the first flag of each target):
 // [first, first + count) in the piece record arrays.
@@ -593,70 +610,235 @@ __device__ __forceinline__ void piece_records(const uint64_t *fbase, const uint6
     count = pos[fbase[q] + (j + 1) * cnt] - first;
 }
 
-__global__ void k_plan_count(const uint64_t *cptr, const unsigned long long *work, const uint64_t *rowptr,
-                             const uint64_t *fbase, const uint64_t *pos, uint32_t n, TileCaps caps,
-                             uint32_t *tcnt /* [classes][n] */)
+// Records of every class (the work tiles' caps follow from them), and the
+// largest d+; one atomic per block and value.
+__global__ __launch_bounds__(kB) void k_plan_records(const uint32_t *incnt, const uint64_t *rowptr, uint32_t n,
+                                                     unsigned long long *rec /* [classes] */)
 {
+    __shared__ unsigned long long tmp[kB / kWave];
+    unsigned long long r[kNumClasses] = {};
     for (size_t q = blockIdx.x * (size_t)blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x) {
-        const uint64_t cnt = cptr[q + 1] - cptr[q];
+        const uint32_t cnt = incnt[q];
+        if (!cnt) continue;
         const int c = class_of(rowptr[q + 1] - rowptr[q]);
-        uint32_t rc = caps.rec[0];
-        uint64_t wc = caps.work[0];
 #pragma unroll
-        for (int i = 1; i < kNumClasses; ++i) {
-            if (i == c) {
-                rc = caps.rec[i];
-                wc = caps.work[i];
-            }
+        for (int i = 0; i < kNumClasses; ++i) r[i] += i == c ? cnt : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kNumClasses; ++i) block_add<kB>(r[i], tmp, &rec[i]);
+}
+
+// The plan in two passes over the targets, kPlanChunk consecutive targets to
+// a block and kPlanItems consecutive ones to a thread.  k_plan_count leaves
+// one column of sums per block (rows below); their exclusive scan, row after
+// row, gives every block the places of its tiles and the host the totals;
+// k_plan_write computes the same counts again and writes the tiles.
+constexpr int kPlanItems = 2;
+constexpr size_t kPlanChunk = (size_t)kB * kPlanItems;
+// rows: tiles and work tiles of each class (target order), then records,
+// staged out-list entries and wedge checks of each class, then all wedge
+// checks and the targets with any
+static_assert(5 * kNumClasses + 2 < kWave, "k_plan_heads takes one lane per row");
+constexpr int kPlanTiles = 0, kPlanWork = kNumClasses, kPlanRec = 2 * kNumClasses, kPlanStaged = 3 * kNumClasses,
+              kPlanProbes = 4 * kNumClasses, kPlanAll = 5 * kNumClasses, kPlanTargets = 5 * kNumClasses + 1,
+              kPlanRows = 5 * kNumClasses + 2;
+
+struct PlanIn {
+    const uint64_t *cptr;             // [n + 1] first record of each target
+    const unsigned long long *work;   // [n] wedge checks of each target
+    const uint64_t *rowptr;
+    const uint64_t *fbase, *pos;      // pieces of huge targets (null without any)
+    const unsigned long long *rec;    // records of each class
+    uint32_t n;
+    TileCaps caps;
+};
+
+struct PlanTarget {
+    int c;             // class
+    uint32_t tiles, work_tiles;
+    uint64_t cnt, work, dq;
+};
+
+// Caps of class c under the plan, and those of its work tiles.
+__device__ __forceinline__ void class_caps(const PlanIn &in, int c, uint32_t &rc, uint64_t &wc, uint32_t &frc, uint64_t &fwc)
+{
+    rc = in.caps.rec[0];
+    wc = in.caps.work[0];
+#pragma unroll
+    for (int i = 1; i < kNumClasses; ++i) {
+        if (i == c) {
+            rc = in.caps.rec[i];
+            wc = in.caps.work[i];
         }
-        uint32_t t = 0;
-        if (c == kClassHuge && cnt) {
-            // each piece of Adj+(q) has its own records and tiles; it sees
-            // about 1/S of the target's wedge checks
-            const uint32_t S = piece_count(rowptr[q + 1] - rowptr[q]);
+    }
+    frc = work_rec_cap(c, rc, in.rec[c]);
+    fwc = min(wc, kTileWorkPerRecord * (uint64_t)frc);
+}
+
+__device__ __forceinline__ PlanTarget plan_target(const PlanIn &in, size_t q)
+{
+    PlanTarget t{};
+    if (q >= in.n) return t;
+    t.cnt = in.cptr[q + 1] - in.cptr[q];
+    if (!t.cnt) return t;
+    t.work = in.work[q];
+    t.dq = in.rowptr[q + 1] - in.rowptr[q];
+    t.c = class_of(t.dq);
+    uint32_t rc, frc;
+    uint64_t wc, fwc;
+    class_caps(in, t.c, rc, wc, frc, fwc);
+    if (t.c == kClassHuge) {
+        // each piece of Adj+(q) has its own records and tiles; it sees
+        // about 1/S of the target's wedge checks
+        const uint32_t S = piece_count(t.dq);
+        for (uint32_t j = 0; j < S; ++j) {
+            uint64_t first, count;
+            piece_records(in.fbase, in.pos, q, j, t.cnt, first, count);
+            t.tiles += tiles_of(count, (t.work + S - 1) / S, rc, wc);
+            t.work_tiles += tiles_of(count, (t.work + S - 1) / S, frc, fwc);
+        }
+    } else {
+        t.tiles = tiles_of(t.cnt, t.work, rc, wc);
+        t.work_tiles = tiles_of(t.cnt, t.work, frc, fwc);
+    }
+    return t;
+}
+
+__global__ __launch_bounds__(kB) void k_plan_count(PlanIn in, uint64_t *sums /* [rows][blocks] */)
+{
+    __shared__ unsigned long long part[kB / kWave][kPlanRows];
+    unsigned long long v[kPlanRows] = {};
+    const size_t q0 = blockIdx.x * kPlanChunk;
+    for (int k = 0; k < kPlanItems; ++k) {
+        const size_t q = q0 + (size_t)k * kB + threadIdx.x;
+        const PlanTarget t = plan_target(in, q);
+        if (!t.cnt) continue;
+        // a huge target: the records cut to its pieces, each piece staged by
+        // each of its tiles
+        uint64_t nrec = t.cnt, staged = (uint64_t)t.tiles * t.dq;
+        if (t.c == kClassHuge) {
+            uint32_t rc, frc;
+            uint64_t wc, fwc;
+            class_caps(in, t.c, rc, wc, frc, fwc);
+            const uint32_t S = piece_count(t.dq), psz = piece_size(t.dq);
+            nrec = 0;
+            staged = 0;
             for (uint32_t j = 0; j < S; ++j) {
                 uint64_t first, count;
-                piece_records(fbase, pos, q, j, cnt, first, count);
-                t += tiles_of(count, (work[q] + S - 1) / S, rc, wc);
+                piece_records(in.fbase, in.pos, q, j, t.cnt, first, count);
+                nrec += count;
+                staged += (uint64_t)tiles_of(count, (t.work + S - 1) / S, rc, wc) *
+                          min((uint64_t)psz, t.dq - (uint64_t)j * psz);
             }
-        } else {
-            t = tiles_of(cnt, work[q], rc, wc);
         }
-        for (int i = 0; i < kNumClasses; ++i) tcnt[(size_t)i * n + q] = (i == c) ? t : 0u;
+#pragma unroll
+        for (int i = 0; i < kNumClasses; ++i) {
+            const bool on = i == t.c;
+            v[kPlanTiles + i] += on ? t.tiles : 0u;
+            v[kPlanWork + i] += on ? t.work_tiles : 0u;
+            v[kPlanRec + i] += on && t.tiles ? nrec : 0u;
+            v[kPlanStaged + i] += on && t.tiles ? staged : 0u;
+            v[kPlanProbes + i] += on && t.tiles ? t.work : 0u;
+        }
+        v[kPlanAll] += t.work;
+        v[kPlanTargets] += t.work ? 1 : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < kPlanRows; ++i) {
+        const unsigned long long x = wave_sum(v[i]);
+        if (lane_id() == 0) part[threadIdx.x / kWave][i] = x;
+    }
+    __syncthreads();
+    if (threadIdx.x < kPlanRows) {
+        unsigned long long x = 0;
+        for (int w = 0; w < kB / kWave; ++w) x += part[w][threadIdx.x];
+        sums[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = x;
     }
 }
 
-// The tiles of target q, dealing its records round-robin; for a huge
-// target, the tiles of each piece in turn over that piece's records.
-__global__ void k_plan_write(const uint64_t *cptr, const unsigned long long *work, const uint64_t *rowptr,
-                             const uint64_t *fbase, const uint64_t *pos, const uint64_t *tile_off,
-                             const uint32_t *tcnt, uint32_t n, TileCaps caps, int cls, TileDesc *tiles)
+// The first place of every row of the scanned sums and, past the last, the end.
+__global__ void k_plan_heads(const uint64_t *sums, unsigned blocks, uint64_t *head /* [rows + 1] */)
 {
-    for (size_t q = blockIdx.x * (size_t)blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x) {
-        const uint32_t t = tcnt[q];
-        if (!t) continue;
-        const uint64_t cnt = cptr[q + 1] - cptr[q];
-        uint64_t at = tile_off[q];
-        auto deal = [&](uint64_t first, uint64_t count, uint32_t tj, uint32_t piece) {
-            for (uint32_t i = 0; i < tj; ++i) {
+    if (threadIdx.x <= kPlanRows) head[threadIdx.x] = sums[(size_t)threadIdx.x * blocks];
+}
+
+struct PlanOut {
+    TileDesc *tiles[kNumClasses];  // null: the class has none, or its work tiles are its tiles
+    TileDesc *work[kNumClasses];
+};
+
+// The tiles of target q, dealing its records round-robin; for a huge target,
+// the tiles of each piece in turn over that piece's records.  Places are in
+// target order: a block's first place from the scanned sums, a thread's from
+// a scan of the block's threads.
+__global__ __launch_bounds__(kB) void k_plan_write(PlanIn in, const uint64_t *sums, PlanOut out)
+{
+    __shared__ uint64_t tmp[kB / kWave];
+    PlanTarget t[kPlanItems];
+    const size_t q0 = blockIdx.x * kPlanChunk + (size_t)threadIdx.x * kPlanItems;
+#pragma unroll
+    for (int k = 0; k < kPlanItems; ++k) t[k] = plan_target(in, q0 + k);
+    for (int list = 0; list < 2; ++list) {
+        for (int c = 0; c < kNumClasses; ++c) {
+            TileDesc *dst = list ? out.work[c] : out.tiles[c];
+            if (!dst) continue;
+            const uint64_t *row = sums + (size_t)((list ? kPlanWork : kPlanTiles) + c) * gridDim.x;
+            uint64_t mine = 0;
+#pragma unroll
+            for (int k = 0; k < kPlanItems; ++k)
+                if (t[k].cnt && t[k].c == c) mine += list ? t[k].work_tiles : t[k].tiles;
+            uint64_t total;
+            uint64_t at = row[blockIdx.x] - row[0] + block_excl_scan<kB>(mine, tmp, total);
+            if (!total) continue;
+            uint32_t rc, frc;
+            uint64_t wc, fwc;
+            class_caps(in, c, rc, wc, frc, fwc);
+            if (list) {
+                rc = frc;
+                wc = fwc;
+            }
+            // a run of tj tiles over `count` records from `first`; a target
+            // with many is written by its whole wave
+            auto put = [&](uint64_t where, uint32_t i, uint32_t q, uint64_t first, uint64_t count, uint32_t tj,
+                           uint32_t piece) {
                 TileDesc d;
-                d.q = (uint32_t)q;
+                d.q = q;
                 d.cnt = (uint32_t)((count - i + tj - 1) / tj);  // records i, i + tj, ...
                 d.e0 = first + i;
                 d.stride = tj;
                 d.piece = piece;
-                tiles[at++] = d;
+                dst[where + i] = d;
+            };
+#pragma unroll
+            for (int k = 0; k < kPlanItems; ++k) {
+                const bool on = t[k].cnt && t[k].c == c;
+                const uint32_t nt = on ? (list ? t[k].work_tiles : t[k].tiles) : 0u;
+                const uint32_t q = (uint32_t)(q0 + k);
+                if (c == kClassHuge) {
+                    if (!on) continue;
+                    const uint32_t S = piece_count(t[k].dq);
+                    for (uint32_t j = 0; j < S; ++j) {
+                        uint64_t first, count;
+                        piece_records(in.fbase, in.pos, q, j, t[k].cnt, first, count);
+                        const uint32_t tj = tiles_of(count, (t[k].work + S - 1) / S, rc, wc);
+                        for (uint32_t i = 0; i < tj; ++i) put(at, i, q, first, count, tj, j);
+                        at += tj;
+                    }
+                    continue;
+                }
+                const uint64_t first = on ? in.cptr[q] : 0;
+                const bool many = nt > 8;
+                if (!many)
+                    for (uint32_t i = 0; i < nt; ++i) put(at, i, q, first, t[k].cnt, nt, 0);
+                for (uint64_t m = __ballot(many); m; m &= m - 1) {
+                    const int l = __ffsll((long long)m) - 1;
+                    const uint64_t lat = __shfl(at, l, kWave), lfirst = __shfl(first, l, kWave),
+                                   lcnt = __shfl(t[k].cnt, l, kWave);
+                    const uint32_t ln = __shfl(nt, l, kWave), lq = __shfl(q, l, kWave);
+                    for (uint32_t i = lane_id(); i < ln; i += kWave) put(lat, i, lq, lfirst, lcnt, ln, 0);
+                }
+                at += nt;
             }
-        };
-        if (cls == kClassHuge) {
-            const uint32_t S = piece_count(rowptr[q + 1] - rowptr[q]);
-            for (uint32_t j = 0; j < S; ++j) {
-                uint64_t first, count;
-                piece_records(fbase, pos, q, j, cnt, first, count);
-                deal(first, count, tiles_of(count, (work[q] + S - 1) / S, caps.rec[cls], caps.work[cls]), j);
-            }
-        } else {
-            deal(cptr[q], cnt, t, 0);
         }
     }
 }
@@ -733,63 +915,6 @@ __global__ void k_piece_cut(const uint64_t *inkey, const uint32_t *inpay, int kb
     }
 }
 
-// Per-class totals of the plan: records, staged out-list entries, probes;
-// then the probes of all targets and the number of targets with any.
-__global__ void k_plan_stats(const uint64_t *cptr, const unsigned long long *work, const uint64_t *rowptr,
-                             const uint64_t *fbase, const uint64_t *pos, const uint32_t *tcnt, uint32_t n,
-                             TileCaps caps, unsigned long long *out /* [3][classes], probes, targets */)
-{
-    unsigned long long rec[kNumClasses] = {}, stg[kNumClasses] = {}, prb[kNumClasses] = {}, wall = 0, wnz = 0;
-    for (size_t q = blockIdx.x * (size_t)blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x) {
-        const unsigned long long wq = work[q];
-        wall += wq;
-        wnz += wq ? 1 : 0;
-        const uint64_t dq = rowptr[q + 1] - rowptr[q];
-        const int c = class_of(dq);
-        const uint32_t t = tcnt[(size_t)c * n + q];
-        if (!t) continue;
-        // a huge target: the records cut to its pieces, each piece staged by
-        // each of its tiles
-        uint64_t nrec = cptr[q + 1] - cptr[q], staged = (uint64_t)t * dq;
-        if (c == kClassHuge) {
-            const uint32_t S = piece_count(dq), psz = piece_size(dq);
-            const uint64_t cnt = nrec;
-            nrec = 0;
-            staged = 0;
-            for (uint32_t j = 0; j < S; ++j) {
-                uint64_t first, count;
-                piece_records(fbase, pos, q, j, cnt, first, count);
-                nrec += count;
-                staged += (uint64_t)tiles_of(count, (work[q] + S - 1) / S, caps.rec[c], caps.work[c]) *
-                          min((uint64_t)psz, dq - (uint64_t)j * psz);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kNumClasses; ++i) {
-            if (i == c) {
-                rec[i] += nrec;
-                stg[i] += staged;
-                prb[i] += wq;
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < kNumClasses; ++i) {
-        const unsigned long long a = wave_sum(rec[i]), b = wave_sum(stg[i]), c = wave_sum(prb[i]);
-        if (lane_id() == 0) {
-            if (a) atomicAdd(&out[0 * kNumClasses + i], a);
-            if (b) atomicAdd(&out[1 * kNumClasses + i], b);
-            if (c) atomicAdd(&out[2 * kNumClasses + i], c);
-        }
-    }
-    wall = wave_sum(wall);
-    wnz = wave_sum(wnz);
-    if (lane_id() == 0) {
-        if (wall) atomicAdd(&out[3 * kNumClasses], wall);
-        if (wnz) atomicAdd(&out[3 * kNumClasses + 1], wnz);
-    }
-}
-
 template <class T>
 T read_scalar(const T *dev, hipStream_t s)
 {
@@ -818,7 +943,7 @@ uint64_t graph_bytes(const tp_graph *g)
                  g->perm.bytes() + g->inkey.bytes() + g->inpay.bytes() + g->rank_gid.bytes() +
                  g->dbin_rank.bytes() + g->dbin_slot.bytes() + g->edir.bytes() + g->piece_key.bytes() +
                  g->piece_pay.bytes();
-    for (int c = 0; c < kNumClasses; ++c) b += g->tiles[c].bytes();
+    for (int c = 0; c < kNumClasses; ++c) b += g->tiles[c].bytes() + g->work_tiles[c].bytes();
     return b;
 }
 
@@ -830,8 +955,10 @@ void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
     const uint32_t n = g->n;
     DArray<unsigned long long> work(n, s);
     DArray<uint64_t> cptr((size_t)n + 1, s);
+    DArray<unsigned long long> rec(kNumClasses, s);
     {
         DArray<uint32_t> incnt(n, s);
+        TP_HIP(hipMemsetAsync(rec.get(), 0, kNumClasses * sizeof(unsigned long long), s));
         TP_HIP(hipMemsetAsync(incnt.get(), 0, n * sizeof(uint32_t), s));
         TP_HIP(hipMemsetAsync(work.get(), 0, n * sizeof(unsigned long long), s));
         if (g->n_in) {
@@ -839,6 +966,8 @@ void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
                                                            work.get(), incnt.get());
             TP_CHECK_LAUNCH();
         }
+        k_plan_records<<<grid_for(n, kB, kStatBlocks), kB, 0, s>>>(incnt.get(), g->rowptr.get(), n, rec.get());
+        TP_CHECK_LAUNCH();
         scan_u32_to_u64(incnt.get(), cptr.get(), n, s);
     }
     // the records of huge targets cut to the pieces of Adj+(q): a flag per
@@ -892,43 +1021,45 @@ void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
         caps.rec[c] = cfg.tile_records[c];
         caps.work[c] = kTileWorkPerRecord * cfg.tile_records[c];
     }
-    DArray<uint32_t> tcnt((size_t)kNumClasses * n, s);
-    k_plan_count<<<grid_for(n, kB), kB, 0, s>>>(cptr.get(), work.get(), g->rowptr.get(), fbase.get(), pos.get(), n,
-                                                caps, tcnt.get());
+    const PlanIn in{cptr.get(), work.get(), g->rowptr.get(), fbase.get(), pos.get(), rec.get(), n, caps};
+    const unsigned nb = (unsigned)((n + kPlanChunk - 1) / kPlanChunk);
+    DArray<uint64_t> sums((size_t)kPlanRows * nb + 1, s), head(kPlanRows + 1, s);
+    k_plan_count<<<nb, kB, 0, s>>>(in, sums.get());
     TP_CHECK_LAUNCH();
+    scan_u64(sums.get(), sums.get(), (size_t)kPlanRows * nb, true, s);
+    k_plan_heads<<<1, kWave, 0, s>>>(sums.get(), nb, head.get());
+    TP_CHECK_LAUNCH();
+    uint64_t first[kPlanRows + 1];
+    TP_HIP(hipMemcpyAsync(first, head.get(), sizeof(first), hipMemcpyDeviceToHost, s));
+    TP_HIP(hipStreamSynchronize(s));
+    auto total = [&](int row) { return first[row + 1] - first[row]; };
+    PlanOut out{};
+    bool any = false;
     for (int c = 0; c < kNumClasses; ++c) {
-        DArray<uint64_t> toff((size_t)n + 1, s);
-        scan_u32_to_u64(tcnt.get() + (size_t)c * n, toff.get(), n, s);
-        const uint64_t nt = read_scalar(toff.get() + n, s);
+        const uint64_t nt = total(kPlanTiles + c), nw = total(kPlanWork + c);
         g->n_tiles[c] = nt;
         g->tiles[c].reset(std::max<uint64_t>(nt, 1), s);
-        if (nt) {
-            k_plan_write<<<grid_for(n, kB), kB, 0, s>>>(cptr.get(), work.get(), g->rowptr.get(), fbase.get(),
-                                                        pos.get(), toff.get(), tcnt.get() + (size_t)c * n, n, caps,
-                                                        c, g->tiles[c].get());
-            TP_CHECK_LAUNCH();
-        }
+        // (a finer cut gives no target fewer tiles: as many in all is the same cut)
+        g->n_work_tiles[c] = nw == nt ? 0 : nw;
+        g->work_tiles[c].reset(g->n_work_tiles[c], s);
+        out.tiles[c] = nt ? g->tiles[c].get() : nullptr;
+        out.work[c] = g->work_tiles[c].get();
+        any = any || nt;
     }
-    // per class: records, staged entries, probes; then all probes and active targets
-    constexpr int kStat = 3 * kNumClasses;
-    DArray<unsigned long long> pst(kStat + 2, s);
-    TP_HIP(hipMemsetAsync(pst.get(), 0, (kStat + 2) * sizeof(unsigned long long), s));
-    k_plan_stats<<<grid_for(n, kB), kB, 0, s>>>(cptr.get(), work.get(), g->rowptr.get(), fbase.get(), pos.get(),
-                                                tcnt.get(), n, caps, pst.get());
-    TP_CHECK_LAUNCH();
-    unsigned long long h[kStat + 2];
-    TP_HIP(hipMemcpyAsync(h, pst.get(), sizeof(h), hipMemcpyDeviceToHost, s));
-    TP_HIP(hipStreamSynchronize(s));
+    if (any) {
+        k_plan_write<<<nb, kB, 0, s>>>(in, sums.get(), out);
+        TP_CHECK_LAUNCH();
+    }
     g->stats.n_tiles = 0;
     for (int c = 0; c < kNumClasses; ++c) {
         g->stats.class_tiles[c] = g->n_tiles[c];
-        g->stats.class_records[c] = h[c];
-        g->stats.class_staged[c] = h[kNumClasses + c];
-        g->stats.class_probes[c] = h[2 * kNumClasses + c];
+        g->stats.class_records[c] = total(kPlanRec + c);
+        g->stats.class_staged[c] = total(kPlanStaged + c);
+        g->stats.class_probes[c] = total(kPlanProbes + c);
         g->stats.n_tiles += g->n_tiles[c];
     }
-    g->stats.probes = h[kStat];
-    g->stats.n_targets = h[kStat + 1];
+    g->stats.probes = total(kPlanAll);
+    g->stats.n_targets = total(kPlanTargets);
     g->plan = cfg;
 }
 

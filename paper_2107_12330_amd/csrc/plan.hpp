@@ -49,6 +49,12 @@ constexpr uint32_t kTileRecords = 1024;
 constexpr uint64_t kTileWorkPerRecord = 256;
 inline uint32_t default_tile_records(int cls) { return cls >= 2 ? 16384u : kTileRecords; }
 
+// Fewest records of a work tile's cap (the finer cut of graphs too small to
+// fill the device): the tiny and small classes, and the larger two, whose
+// tables take longer to fill.
+constexpr uint32_t kWorkRecMin = 32;
+constexpr uint32_t kWorkRecMinLarge = 512;
+
 // Slots of padding after the last oriented edge in the target and time
 // arrays, so that a wave may load 64 consecutive slots from any row start.
 constexpr uint64_t kRowPad = 64;

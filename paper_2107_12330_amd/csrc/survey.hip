@@ -55,14 +55,20 @@ template <bool WAVE> struct Depth {
     static constexpr uint32_t kChunkCand = kSub * 64;
 };
 constexpr uint32_t kRing = 128;    // per-wave ring of queued hits: slot|label(p), time(p,r), time(p,q), p
-// Tiles claimed with one atomic on the tile counter: at most 8 by a workgroup
-// and 16 by a wave of the per-wave form, fewer when the class has too few
+// Tiles claimed at a time: at most 8 by a workgroup, 4 by a wave of the
+// per-wave form (out of the block of kWaveClaims times as many that its
+// workgroup claims); in a batch 2 and 2.  Fewer when the class has too few
 // tiles for every claimer to make about 8 claims (the tail stays balanced).
-// Every claim is an atomic on one counter, which at 131 M tiny tiles (the
-// 20,000-graph batch) serialises: 8 per wave took that batch's survey to
-// 515 ms, 16 per wave and 8 per workgroup to about 450 ms.
+// The fewer tiles are claimed at a time, the closer together the device
+// works and the more rows of the graph its caches share; the more claims, the
+// longer the claim counter takes.  Tiles per workgroup's block of the
+// per-wave form, 64 / 32 / 16: 1200-graph batch 13.1 / 10.1 / 9.0 ms (of its
+// tiny class), scale 26 6.3 / 4.5 / 5.2 ms.  Tiles per workgroup, 8 / 4 / 2 /
+// 1: 300-graph batch 2.78 / 2.19 / 1.99 / 2.00 ms (small class), scale 26
+// 99.7 / 100.2 / 103.4 / 116.5 ms.
 constexpr uint32_t kMaxClaimGroup = 8;
-constexpr uint32_t kMaxClaimWave = 16;
+constexpr uint32_t kMaxClaimWave = 4;
+constexpr uint32_t kMaxClaimBatch = 2;
 // The tiles of a batch's launch are cut into kClaimSegs contiguous segments,
 // one per XCD, each with its own claim counter.  Workgroups are dispatched to
 // the 8 XCDs round robin, so workgroup b starts on segment b % 8: the waves of
@@ -74,6 +80,7 @@ constexpr uint32_t kMaxClaimWave = 16;
 // device-wide last-level cache then holds once (scale 26: tiny class 8 ms
 // with one counter, 14 ms with eight).
 constexpr uint32_t kClaimSegs = 8;
+static_assert(kNumClasses <= kClaimWords, "one claim counter per class of a single graph");
 static_assert(kClaimSegs <= kClaimWords && kClaimSegs == 8, "one claim counter per segment, 2^3 segments");
 constexpr int kRsrcWord3 = 0x00020000;  // buffer resource word 3 for raw 32-bit loads on CDNA
 constexpr uint32_t kEmpty = 0xffffffffu;
@@ -176,14 +183,14 @@ struct SurveyParams {
     uint32_t grid_eighths;    // share of the device the persistent grid may fill (0 or 8: all)
     uint32_t claim;           // tiles a wave (per-wave form) or workgroup claims at a time
     uint32_t claim_seg_log;   // log2 of the claim segments (0 or 3)
+    uint32_t clear_claims;    // host: clear the claim counters before the launch
     // exact counting set of Algorithm 3 (extended form): an open-addressing
     // table of maxe_mask + 1 slots; key value + 1 (0: empty) and its count
     unsigned long long *maxe_keys;
     unsigned long long *maxe_counts;
     uint64_t maxe_mask;
     unsigned *maxe_overflow;  // set when a value finds no slot
-    // single-graph surveys: after class c, the running triangle count is
-    // copied to class_tri[c] (so that each class's triangles are known)
+    // single-graph surveys: class c counts its triangles at class_tri[c]
     unsigned long long *class_tri;
 };
 
@@ -486,6 +493,62 @@ struct RecBlock {
     uint32_t p;     // rank of p (enumeration)
 };
 
+// Claims of the per-wave form.  The waves of a workgroup share a block of
+// kWaveClaims * P.claim consecutive tiles, claimed with one atomic on a device
+// counter, and take P.claim tiles of it at a time with an LDS atomic: the
+// device counter takes one claim in about 20 ns, and the 476,000 claims of a
+// 1200-graph batch's tiny tiles took 10 of the kernel's 12.9 ms.  (Dealing
+// tiles out beforehand takes no counter at all, but lets the waves drift
+// apart: neighbouring tiles share rows of the graph in cache only while they
+// run at the same time; that batch's tiny class then took 20.5 ms.)
+// state: first tile of the block << 19 | its segment << 16 | tiles handed out;
+// the wave whose add is the first past the block's end claims the next block,
+// the others wait for it.
+constexpr uint32_t kWaveClaims = 8;
+constexpr uint64_t kNoTiles = ~0ull;
+constexpr uint64_t kClaimFresh = (1ull << 48) - 1;  // no block yet
+constexpr uint64_t kClaimDone = (1ull << 48) - 2;   // no tile left
+struct ClaimBlock {
+    unsigned long long state;
+    uint32_t seg, left;  // the claiming wave's: segment in use, segments not used up
+};
+
+// First tile << 3 | segment of the next P.claim tiles (which may lie past the
+// segment's end: then there are none), or kNoTiles.  Called by one lane.
+__device__ __forceinline__ uint64_t claim_tiles(const SurveyParams &P, ClaimBlock &cb, uint32_t nseg)
+{
+    const uint64_t step = P.claim ? P.claim : 1u, size = step * kWaveClaims;
+    for (;;) {
+        const uint64_t old = __hip_atomic_fetch_add(&cb.state, step, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint64_t block = old >> 16, off = old & 0xffffu;
+        if (block == kClaimDone) return kNoTiles;
+        if (off < size) return (((block >> 3) + off) << 3) | (block & 7u);
+        if (off == size) {
+            // this wave's: it alone changes seg and left until it publishes
+            uint32_t seg = cb.seg;
+            for (;;) {
+                const uint64_t lo = (P.n_tiles * seg) >> P.claim_seg_log, hi = (P.n_tiles * (seg + 1)) >> P.claim_seg_log;
+                const uint64_t t = lo + atomicAdd(P.tile_counter + seg, 1ull) * size;
+                if (t < hi) {
+                    const uint64_t next = (t << 3) | seg;
+                    cb.seg = seg;
+                    __hip_atomic_store(&cb.state, (next << 16) | step, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    return next;
+                }
+                // the segment is used up (its counter only grows): the next one
+                if (--cb.left == 0) {
+                    __hip_atomic_store(&cb.state, kClaimDone << 16, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    return kNoTiles;
+                }
+                seg = (seg + 1) & (nseg - 1);
+            }
+        }
+        // another wave of this workgroup is claiming the next block
+        while ((__hip_atomic_load(&cb.state, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >> 16) == block)
+            __builtin_amdgcn_s_sleep(1);
+    }
+}
+
 // LOG_SLOTS > 0: LDS hash of Adj+(q) with 2^LOG_SLOTS slots at most.
 // LOG_SLOTS == 0: binary search of Adj+(q) in HBM.
 // WAVE == false: the BLOCK threads of a workgroup share one target's table
@@ -562,7 +625,9 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
     __shared__ uint8_t dtype_lds[EXT ? 64 : 1];
     __shared__ SlotSpec slot_lds[MULTI ? kMaxSlots : 1];
     __shared__ unsigned long long s_tile;
+    __shared__ ClaimBlock s_claim;  // WAVE
     __shared__ uint32_t s_stash_g[kGroups], s_fail_g[kGroups];
+    __shared__ unsigned long long s_tot[3];  // triangles, spread count, probes (flush_all)
     uint32_t &s_stash = s_stash_g[grp];
     uint32_t &s_fail = s_fail_g[grp];
     // barrier of the threads that share a table
@@ -580,6 +645,12 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
     uint4 *ring = reinterpret_cast<uint4 *>(lds + L.off_ring) + (size_t)w * kRingK;
     for (uint32_t i = tid; i < nc * kGroups; i += BLOCK) cnt_all[i] = 0;
     if (tid < 13) mask_lds[tid] = P.label_mask[tid];
+    if (tid < 3) s_tot[tid] = 0;
+    if (WAVE && tid == 0) {
+        s_claim.state = (kClaimFresh << 16) | (kClaim * kWaveClaims);
+        s_claim.seg = blockIdx.x & ((1u << P.claim_seg_log) - 1u);
+        s_claim.left = 1u << P.claim_seg_log;
+    }
     if (EXT && (P.outputs & TP_OUT_DEGREE_TABLE))
         for (int i = tid; i < kGroups * 32; i += BLOCK) dbin_lds[i] = P.dbin_rank[i & 31];
     if (EXT && tid < 64) dtype_lds[tid] = P.dir_type[tid];
@@ -598,12 +669,13 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
     unsigned long long my_tri = 0, my_spread = 0, probes = 0;
     uint32_t qh = 0, qt = 0;  // this wave's hit ring: entries [qh, qt)
 
-    // merge this workgroup's counters into graph g's result block; every
-    // thread of the workgroup calls it
+    // merge this group's counters into graph g's result block (batches, at a
+    // change of graph: one copy of each counter); every thread of the group
+    // calls it
     auto flush = [&](uint32_t g) {
         unsigned long long *blk = P.out + (size_t)g * P.g_stride;
         const unsigned long long t = wave_sum(my_tri), sp = wave_sum(my_spread);
-        if (lane == 0 && !MULTI) {
+        if (lane == 0) {
             if (t) atomicAdd(&blk[P.o_tri], t);
             if (sp) atomicAdd(&blk[P.o_spread], sp);
             if (probes) atomicAdd(&blk[P.o_probes], probes);
@@ -616,13 +688,6 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
             const unsigned long long v = cnt[i];
             if (!v) continue;
             uint32_t word;
-            if (MULTI) {
-                // slot i / slot_words, at the same word of its block
-                const uint32_t sl = i / P.slot_words;
-                atomicAdd(&P.out[(size_t)sl * P.g_stride + (i - sl * P.slot_words)], v);
-                cnt[i] = 0;
-                continue;
-            }
             const CounterBase B = counter_base(P, EXT);
             if (i < B.table) word = P.o_hist + i / P.copies;
             else if (i < B.oc) word = P.o_table + (i - B.table) / P.copies;
@@ -634,6 +699,53 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
             cnt[i] = 0;
         }
         gsync();
+    };
+    // Merge the workgroup's counters into the result as it retires (graph g of
+    // a batch).  The waves' sums and the copies of each counter are added up in
+    // LDS first, so that a word takes one device atomic per workgroup: adds to
+    // one address serialise at some 12 ns each, and a small graph's few tiles
+    // are spread over as many waves as there are (scale 13, 2168 waves of 4
+    // copies each: 247 us for 677,000 checks).
+    auto flush_all = [&](uint32_t g) {
+        unsigned long long *blk = P.out + (size_t)g * P.g_stride;
+        const unsigned long long t = wave_sum(my_tri), sp = wave_sum(my_spread);
+        if (lane == 0 && !MULTI) {
+            if (t) atomicAdd(&s_tot[0], t);
+            if (sp) atomicAdd(&s_tot[1], sp);
+            if (probes) atomicAdd(&s_tot[2], probes);
+        }
+        __syncthreads();
+        if (!MULTI && tid < 3) {
+            const unsigned long long v = s_tot[tid];
+            if (v) atomicAdd(&blk[tid == 0 ? P.o_tri : (tid == 1 ? P.o_spread : P.o_probes)], v);
+        }
+        // counter i of every group (of a histogram or table word: all copies)
+        const CounterBase B = counter_base(P, EXT);
+        const uint32_t step = MULTI ? 1u : P.copies;
+        const uint32_t copied = MULTI ? 0u : B.oc;  // the words before it are held in copies
+        const uint32_t nw = copied / step + (nc - copied);
+        for (uint32_t j = tid; j < nw; j += BLOCK) {
+            const bool many = j < copied / step;
+            const uint32_t i = many ? j * step : j - copied / step + copied;
+            unsigned long long v = 0;
+            for (uint32_t x = 0; x < (uint32_t)kGroups; ++x)
+                for (uint32_t k = 0; k < (many ? step : 1u); ++k) v += cnt_all[(size_t)x * nc + i + k];
+            if (!v) continue;
+            uint32_t word;
+            if (MULTI) {
+                // slot i / slot_words, at the same word of its block
+                const uint32_t sl = i / P.slot_words;
+                atomicAdd(&P.out[(size_t)sl * P.g_stride + (i - sl * P.slot_words)], v);
+                continue;
+            }
+            if (i < B.table) word = P.o_hist + j;
+            else if (i < B.oc) word = P.o_table + (j - 32u);
+            else if (!EXT || i < B.maxe) word = P.o_oc + (i - B.oc);
+            else if (i < B.deg) word = P.o_maxe + (i - B.maxe);
+            else if (i < B.dir) word = P.o_deg + (i - B.deg);
+            else word = P.o_dir + (i - B.dir);
+            atomicAdd(&blk[word], v);
+        }
     };
     uint32_t cur_g = 0;  // graph whose counters the workgroup holds
     uint64_t cur_tile = 0;  // global index of the tile being walked (enumeration)
@@ -799,31 +911,35 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
     const uint32_t nseg = 1u << P.claim_seg_log;
     uint32_t seg = blockIdx.x & (nseg - 1);
     uint32_t segs_left = nseg;
-    uint64_t seg_lo = (P.n_tiles * seg) >> P.claim_seg_log;
-    uint64_t seg_hi = (P.n_tiles * (seg + 1)) >> P.claim_seg_log;
+    auto seg_begin = [&](uint32_t x) -> uint64_t { return (P.n_tiles * x) >> P.claim_seg_log; };
+    uint64_t seg_lo = seg_begin(seg), seg_hi = seg_begin(seg + 1);
     for (;;) {
         // claim a chunk of kClaim consecutive tiles; consecutive tiles mostly
         // share their target, whose table is then built once
         uint64_t t_begin;
-        if (WAVE) {
-            unsigned long long c = 0;
-            if (lane == 0) c = atomicAdd(P.tile_counter + seg, 1ull);
-            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)c);
-            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(c >> 32));
-            t_begin = seg_lo + (((uint64_t)hi << 32) | lo) * kClaim;
+        if constexpr (WAVE) {
+            // from the workgroup's block of kWaveClaims chunks (claim_tiles)
+            uint64_t v = 0;
+            if (lane == 0) v = claim_tiles(P, s_claim, nseg);
+            v = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
+                (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+            if (v == kNoTiles) break;
+            t_begin = v >> 3;
+            seg_hi = seg_begin((uint32_t)(v & 7u) + 1u);
+            if (t_begin >= seg_hi) continue;
         } else {
             if (tid == 0) s_tile = atomicAdd(P.tile_counter + seg, 1ull);
             __syncthreads();
             t_begin = seg_lo + s_tile * kClaim;
             __syncthreads();  // everyone has read s_tile before it is claimed again
-        }
-        if (t_begin >= seg_hi) {
-            // the segment is used up (its counter only grows): the next one
-            if (--segs_left == 0) break;
-            seg = (seg + 1) & (nseg - 1);
-            seg_lo = (P.n_tiles * seg) >> P.claim_seg_log;
-            seg_hi = (P.n_tiles * (seg + 1)) >> P.claim_seg_log;
-            continue;
+            if (t_begin >= seg_hi) {
+                // the segment is used up (its counter only grows): the next one
+                if (--segs_left == 0) break;
+                seg = (seg + 1) & (nseg - 1);
+                seg_lo = seg_begin(seg);
+                seg_hi = seg_begin(seg + 1);
+                continue;
+            }
         }
         const uint64_t t_end = min(t_begin + kClaim, seg_hi);
         for (uint64_t ti = t_begin; ti < t_end; ++ti) {
@@ -851,7 +967,7 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                 // against the old table, then rebuild it once every wave is
                 // done with it
                 if (META || ENUM) drain_queued();
-                if (P.rank_gid) {
+                if (!MULTI && P.rank_gid) {
                     const uint32_t g = sload(P.rank_gid + d.q);
                     if (g != cur_g) {
                         flush(cur_g);
@@ -1395,14 +1511,23 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
         gsync();
         flush_part();
     }
-    // ---- merge this workgroup's counters into the result
-    flush(cur_g);
+    // ---- merge this workgroup's counters into the result (the waves of a
+    // batch's per-wave form each hold a graph of their own)
+    if (WAVE && !MULTI && P.rank_gid) flush(cur_g);
+    else flush_all(cur_g);
 }
 
-// dst = *src, by one thread (a snapshot of a counter between launches)
-__global__ void k_copy_word(const unsigned long long *src, unsigned long long *dst)
+// The classes' triangles, summed in place to running sums over the classes,
+// and their total.
+__global__ void k_class_sums(unsigned long long *class_tri, unsigned long long *total)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *src;
+    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    unsigned long long t = 0;
+    for (int c = 0; c < kNumClasses; ++c) {
+        t += class_tri[c];
+        class_tri[c] = t;
+    }
+    *total = t;
 }
 
 __global__ void zero_u64(unsigned long long *p, size_t n)
@@ -1533,7 +1658,7 @@ void launch_kernel(const SurveyParams &P, const LdsLayout &L, hipStream_t s, int
     // workgroup of a full grid
     SurveyParams Q = P;
     const uint64_t units = fit * groups;
-    uint32_t claim = WAVE ? kMaxClaimWave : kMaxClaimGroup;
+    uint32_t claim = P.rank_gid ? kMaxClaimBatch : (WAVE ? kMaxClaimWave : kMaxClaimGroup);
     while (claim > 1 && Q.n_tiles < (uint64_t)claim * units * 8) claim >>= 1;
     Q.claim = claim;
     Q.claim_seg_log = P.rank_gid ? 3u : 0u;  // segments per XCD for batches (kClaimSegs)
@@ -1541,8 +1666,10 @@ void launch_kernel(const SurveyParams &P, const LdsLayout &L, hipStream_t s, int
     uint64_t grid = fit;
     if (P.grid_eighths > 0 && P.grid_eighths < 8) grid = std::max<uint64_t>(1, fit * P.grid_eighths / 8);
     if (grid > claims) grid = claims;
-    zero_u64<<<1, 64, 0, s>>>(Q.tile_counter, kClaimSegs);
-    TP_CHECK_LAUNCH();
+    if (P.clear_claims) {
+        zero_u64<<<1, 64, 0, s>>>(Q.tile_counter, kClaimSegs);
+        TP_CHECK_LAUNCH();
+    }
     kern<<<(unsigned)grid, BLOCK, L.total, s>>>(Q);
     TP_CHECK_LAUNCH();
 }
@@ -1663,21 +1790,30 @@ void launch_variant(int c, uint32_t v, const SurveyParams &P0, hipStream_t s, in
     }
 }
 
-// Launch the target classes in turn.  `timers`, when given, holds one
-// EventTimer per class around its launch.
+// Launch the target classes in turn, into result words and claim counters
+// that the caller has cleared.  `timers`, when given, holds one EventTimer per
+// class around its launch.
 template <bool META, bool ENUM, int FORM = kFormSurvey>
 void launch_all(const tp_graph *g, SurveyParams P, uint32_t strategy, hipStream_t s, EventTimer *timers = nullptr)
 {
+    // a single graph's class has a claim counter of its own; a batch's
+    // classes share the segments' counters and clear them in between
+    unsigned long long *const counters = P.tile_counter;
+    const uint32_t o_tri = P.o_tri;
+    P.clear_claims = 0;
     for (int c = 0; c < kNumClasses; ++c) {
-        P.tiles = g->tiles[c].get();
-        P.n_tiles = g->n_tiles[c];
+        P.tiles = g->survey_tiles(c);
+        P.n_tiles = g->n_survey_tiles(c);
+        if (!P.rank_gid) P.tile_counter = counters + c;
+        if (P.class_tri) P.o_tri = (uint32_t)(P.class_tri - P.out) + c;
         if (timers) timers[c].start();
         launch_variant<META, ENUM, false, FORM>(c, resolve_variant(g, c, strategy), P, s, g->device);
         if (timers) timers[c].stop();
-        if (P.class_tri) {
-            k_copy_word<<<1, 64, 0, s>>>(P.out + P.o_tri, P.class_tri + c);
-            TP_CHECK_LAUNCH();
-        }
+        if (P.rank_gid && P.n_tiles) P.clear_claims = 1;
+    }
+    if (P.class_tri) {
+        k_class_sums<<<1, 64, 0, s>>>(P.class_tri, P.out + o_tri);
+        TP_CHECK_LAUNCH();
     }
 }
 
@@ -1751,6 +1887,7 @@ SurveyParams make_params(const tp_graph *g, const tp_survey_spec *sp, unsigned l
     P.piece_pay = g->piece_pay.get();
     P.kbits = g->kbits;
     P.tile_counter = counter;
+    P.clear_claims = 1;
     P.out = out;
     P.rank_gid = nullptr;
     P.g_stride = 0;
@@ -2421,11 +2558,11 @@ void tp::multi_segment_enqueue(const tp_graph *g, const SlotSpec *dev_slots, uin
         while ((1u << P.lut_shift) < n_labels) ++P.lut_shift;
     P.grid_eighths = grid_eighths;
     for (int c = 0; c < kNumClasses; ++c) {
-        const uint64_t nt = g->n_tiles[c];
+        const uint64_t nt = g->n_survey_tiles(c);
         const uint64_t a = nt * seg / n_seg, b = nt * (seg + 1) / n_seg;
         if (a == b) continue;
         // the kernel walks its tile list from the end
-        P.tiles = g->tiles[c].get() + a;
+        P.tiles = g->survey_tiles(c) + a;
         P.n_tiles = b - a;
         launch_variant<true, false, true>(c, resolve_variant(g, c, TP_STRAT_AUTO), P, s, g->device);
     }
@@ -2440,10 +2577,10 @@ void tp::solo_segment_enqueue(const tp_graph *g, const tp_survey_spec *sp, unsig
     SurveyParams P = make_params(g, sp, dev_out, dev_out + kRwClaim);
     P.grid_eighths = grid_eighths;
     for (int c = 0; c < kNumClasses; ++c) {
-        const uint64_t nt = g->n_tiles[c];
+        const uint64_t nt = g->n_survey_tiles(c);
         const uint64_t a = nt * seg / n_seg, b = nt * (seg + 1) / n_seg;
         if (a == b) continue;
-        P.tiles = g->tiles[c].get() + a;
+        P.tiles = g->survey_tiles(c) + a;
         P.n_tiles = b - a;
         const uint32_t v = resolve_variant(g, c, sp->strategy);
         if (needs_ext(sp)) launch_variant<true, false, false, kFormExt>(c, v, P, s, g->device);
@@ -2500,8 +2637,8 @@ float time_class(const tp_graph *g, const tp_survey_spec *sp, unsigned long long
                  hipStream_t s)
 {
     SurveyParams P = make_params(g, sp, buf, buf + kRwClaim);
-    P.tiles = g->tiles[c].get();
-    P.n_tiles = g->n_tiles[c];
+    P.tiles = g->survey_tiles(c);
+    P.n_tiles = g->n_survey_tiles(c);
     float best = 0.f;
     for (int r = 0; r < reps; ++r) {
         EventTimer t(s);
