@@ -324,11 +324,11 @@ tp_status tripoll_survey_async(const tp_graph *g, const tp_survey_spec *spec, ui
  *   dev_counts  device buffer of `capacity` uint64 owned by the caller: the
  *               number of triangles of each value
  *   n_values    host: the number of distinct values written
- * Synchronous with respect to the host.  Works in a device table of 2^k >=
- * 2 m entries of 16 bytes (m: oriented edges, at most 2^32 entries),
- * allocated for the call; each counted triangle costs two device-scope
- * atomics there, so the call is slower than the binned output.  At most m
- * values exist, so capacity = m always suffices.
+ * Synchronous with respect to the host.  Works in device temporaries of at
+ * most about 20 bytes per oriented edge, allocated for the call: each counted
+ * triangle adds one at its edge of the largest time, and the edges' counts
+ * are then sorted and summed by time.  At most m values exist (m: oriented
+ * edges), so capacity = m always suffices.
  * Errors: TP_ERR_INVALID for a null pointer or a spec tripoll_survey
  * refuses, and when more than `capacity` distinct values exist (then
  * *n_values holds their number and the buffers are untouched);

@@ -476,6 +476,12 @@ bool radix_sort_pairs(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32
     return radix_sort<uint64_t>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
 }
 
+bool radix_sort_pairs32(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt, size_t n, int bits,
+                        hipStream_t s)
+{
+    return radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, s, 0);
+}
+
 bool radix_sort_u32(uint32_t *keys, uint32_t *keys_alt, size_t n, int bits, hipStream_t s, int begin_bit)
 {
     return radix_sort<uint32_t>(keys, nullptr, keys_alt, nullptr, n, bits, s, begin_bit);

@@ -152,7 +152,11 @@ struct SurveyParams {
     uint32_t o_dir;
     const uint8_t *edir;      // directions of the oriented edges (directed builds)
     uint8_t dir_type[64];     // triangle type by dir(p,q) << 4 | dir(p,r) << 2 | dir(q,r); 7 for none
-    unsigned long long *part_edge;  // participation: one counter per CSR slot
+    // participation: one counter per CSR slot.  A count is at most n - 2, and
+    // 32-bit counters halve the lines that a wave's adds to consecutive slots
+    // touch (scale 22, small class: 29.2 -> 18.7 ms).
+    uint32_t *part_edge;
+    uint32_t part_top;  // count only distinct-label triangles, at their edge of the largest time
     const uint32_t *dbin_rank;  // [32 per graph] first rank of degree bin >= k (DEGREE_TABLE)
     const uint64_t *dbin_slot;  // [32 per graph] first CSR slot of a rank of degree bin >= k
     uint32_t t_lo32, t_hi32;  // window, clamped to the uint32 time range
@@ -184,12 +188,6 @@ struct SurveyParams {
     uint32_t claim;           // tiles a wave (per-wave form) or workgroup claims at a time
     uint32_t claim_seg_log;   // log2 of the claim segments (0 or 3)
     uint32_t clear_claims;    // host: clear the claim counters before the launch
-    // exact counting set of Algorithm 3 (extended form): an open-addressing
-    // table of maxe_mask + 1 slots; key value + 1 (0: empty) and its count
-    unsigned long long *maxe_keys;
-    unsigned long long *maxe_counts;
-    uint64_t maxe_mask;
-    unsigned *maxe_overflow;  // set when a value finds no slot
     // single-graph surveys: class c counts its triangles at class_tri[c]
     unsigned long long *class_tri;
 };
@@ -331,33 +329,6 @@ __device__ __forceinline__ bool passes_filters(const SurveyParams &P, const Hit 
     return true;
 }
 
-// One more triangle whose largest edge time is v, in the exact counting set:
-// linear probing from a hash of v (the "lowbias32" integer mixer published
-// with C. Wellons' hash-prospector); a slot, once claimed by a compare
-// and swap, keeps its value, so a plain read that already shows v (or any
-// other value) is final and only an empty-looking slot needs the atomic.
-__device__ __forceinline__ void maxe_count(const SurveyParams &P, uint32_t v)
-{
-    const unsigned long long key = (unsigned long long)v + 1ull;
-    uint32_t x = v;
-    x ^= x >> 16;
-    x *= 0x7feb352du;
-    x ^= x >> 15;
-    x *= 0x846ca68bu;
-    x ^= x >> 16;
-    uint64_t s = x & P.maxe_mask;
-    for (uint64_t probe = 0; probe <= P.maxe_mask; ++probe) {
-        unsigned long long k = __hip_atomic_load(P.maxe_keys + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (k == 0ull) k = atomicCAS(P.maxe_keys + s, 0ull, key);
-        if (k == 0ull || k == key) {
-            atomicAdd(P.maxe_counts + s, 1ull);
-            return;
-        }
-        s = (s + 1) & P.maxe_mask;
-    }
-    atomicOr(P.maxe_overflow, 1u);
-}
-
 template <bool EXT, bool ARITH = false>
 __device__ __forceinline__ uint32_t reduce_hit(const SurveyParams &P, const Hit &h, unsigned long long *cnt,
                                                const uint64_t *mask_lds, const uint16_t *lut, uint32_t &spread)
@@ -392,15 +363,27 @@ __device__ __forceinline__ uint32_t reduce_hit(const SurveyParams &P, const Hit 
         if (h.l_p != h.l_q && h.l_q != h.l_r && h.l_p != h.l_r)
             atomicAdd(&cnt[B.maxe + min(t3 >> P.max_edge_shift, 1023u)], 1ull);
     }
-    if (EXT && P.maxe_keys) {
-        // Algorithm 3's exact counting set: the same triangles, every value kept
-        if (h.l_p != h.l_q && h.l_q != h.l_r && h.l_p != h.l_r) maxe_count(P, t3);
-    }
     if (EXT && (P.outputs & TP_OUT_DEGREE_TABLE))
         atomicAdd(&cnt[B.deg + multiset_index(h.b_p, h.b_q, h.b_r)], 1ull);
     if (EXT && (P.outputs & TP_OUT_DIRECTED))
         atomicAdd(&cnt[B.dir + h.dtype], 1ull);
     return 1;
+}
+
+// Participation: does the triangle pass the prefilters and, with part_top,
+// have three distinct labels?  `at`: the edge that counts it then, one of
+// (p, q), (p, r), (q, r) whose time is the largest; every one without.
+enum { kAtAll = 0, kAtPQ = 1, kAtPR = 2, kAtQR = 3 };
+template <bool ARITH>
+__device__ __forceinline__ bool part_passes(const SurveyParams &P, const Hit &h, const uint64_t *mask_lds,
+                                            const uint16_t *lut, uint32_t &at)
+{
+    bool pass = !P.filters || passes_filters<ARITH>(P, h, mask_lds, lut);
+    if (P.part_top) {
+        pass = pass && h.l_p != h.l_q && h.l_q != h.l_r && h.l_p != h.l_r;
+        at = h.t_pq >= max(h.t_pr, h.t_qr) ? kAtPQ : (h.t_pr >= h.t_qr ? kAtPR : kAtQR);
+    }
+    return pass;
 }
 
 // Degree bin of rank x: the largest k with first[k] <= x (first[0] = 0 and
@@ -563,7 +546,9 @@ __device__ __forceinline__ uint64_t claim_tiles(const SurveyParams &P, ClaimBloc
 // FORM: kFormSurvey for the reductions above; kFormExt adds the extended
 // reductions (max-edge bins, degree table), compiled into their own kernels
 // so that the others keep their register budget; kFormPart counts the
-// triangles at every edge (local participation) instead of reducing them.
+// triangles at every edge (local participation) instead of reducing them, or
+// each triangle at its edge of the largest time (the exact counting set of
+// Algorithm 3, whose values are times of edges).
 // PIECES: the huge class, whose tiles each hold one piece of Adj+(q) and
 // walk records cut to it (the other classes compile without this).
 // The per-wave form of the plain survey is held to 64 registers, 8 waves
@@ -903,7 +888,7 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
         for (uint32_t h = gtid; h < top; h += kGroup) {
             if (hkey[h] == kEmpty) continue;
             const uint32_t c = hcnt[h];
-            if (c) atomicAdd(&P.part_edge[kq + hpos[h]], (unsigned long long)c);
+            if (c) atomicAdd(&P.part_edge[kq + hpos[h]], c);
         }
     };
 
@@ -1208,19 +1193,18 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                             // passes the prefilters: (p, r) by its slot, (q, r)
                             // per table slot, (p, q) once per record group
                             bool pass = (m >> lane) & 1ull;
-                            if (pass && P.filters) {
+                            uint32_t at = kAtAll;
+                            if (pass && (P.filters || P.part_top)) {
                                 Hit h{st.tpq, st.tpr, hts[slot], st.lp, l_q, hlab[slot], 0, 0, 0, 0};
-                                pass = passes_filters<WAVE>(P, h, mask_lds, lut);
+                                pass = part_passes<WAVE>(P, h, mask_lds, lut, at);
                             }
-                            const uint64_t pm = __ballot(pass);
-                            if (pass) {
-                                atomicAdd(&P.part_edge[st.pr], 1ull);
-                                atomicAdd(&hcnt[slot], 1u);
-                            }
+                            if (pass && (at == kAtAll || at == kAtPR)) atomicAdd(&P.part_edge[st.pr], 1u);
+                            if (pass && (at == kAtAll || at == kAtQR)) atomicAdd(&hcnt[slot], 1u);
                             const uint64_t gm_mask = (kRecLanes == 64 ? ~0ull : ((1ull << kRecLanes) - 1)) << lead;
-                            const uint32_t in_group = (uint32_t)__popcll(pm & gm_mask);
-                            if (sub == 0 && in_group) atomicAdd(&P.part_edge[st.pq], (unsigned long long)in_group);
-                            wave_hits += (uint32_t)__popcll(pm);
+                            const uint64_t qm = __ballot(pass && (at == kAtAll || at == kAtPQ));
+                            const uint32_t in_group = (uint32_t)__popcll(qm & gm_mask);
+                            if (sub == 0 && in_group) atomicAdd(&P.part_edge[st.pq], in_group);
+                            wave_hits += (uint32_t)__popcll(__ballot(pass));
                             return;
                         }
                         if (m) {
@@ -1310,6 +1294,13 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                 WaveRec rec = read_rec(0);
                 uint32_t off = 0; // next slot of the current record
                 uint32_t wave_work = 0, wave_hits = 0;
+                // participation: the record whose (p, q) the wave is counting
+                uint64_t pq_slot = 0;
+                uint32_t pq_hits = 0;
+                auto flush_pq = [&]() {
+                    if (PART && pq_hits && lane == 0) atomicAdd(&P.part_edge[pq_slot], pq_hits);
+                    pq_hits = 0;
+                };
 
                 // next chunk of up to kChunkCand candidates of the current
                 // record: its size and the record's metadata; returns the
@@ -1434,7 +1425,8 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                                 // local participation: one count for each edge of
                                 // every triangle that passes the prefilters
                                 bool pass = (m >> lane) & 1ull;
-                                if (pass && P.filters) {
+                                uint32_t at = kAtAll;
+                                if (pass && (P.filters || P.part_top)) {
                                     Hit h{chs[c].t_pq, tpr[c][sr], 0, chs[c].l_p, l_q, 0, 0, 0, 0};
                                     if constexpr (!G) {
                                         h.t_qr = hts[slot];
@@ -1443,18 +1435,21 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                                         h.t_qr = P.ets[kq + slot];
                                         h.l_r = P.tlab[kq + slot];
                                     }
-                                    pass = passes_filters<WAVE>(P, h, mask_lds, lut);
+                                    pass = part_passes<WAVE>(P, h, mask_lds, lut, at);
                                 }
-                                const uint64_t pm = __ballot(pass);
-                                if (pass) {
-                                    atomicAdd(&P.part_edge[chs[c].base + (uint32_t)(sr * kWave) + lane], 1ull);  // (p, r)
+                                if (pass && (at == kAtAll || at == kAtPR))
+                                    atomicAdd(&P.part_edge[chs[c].base + (uint32_t)(sr * kWave) + lane], 1u);  // (p, r)
+                                if (pass && (at == kAtAll || at == kAtQR)) {
                                     if constexpr (!G) atomicAdd(&hcnt[slot], 1u);  // (q, r), per table slot
-                                    else atomicAdd(&P.part_edge[kq + slot], 1ull);
+                                    else atomicAdd(&P.part_edge[kq + slot], 1u);
                                 }
-                                if (pm) {
-                                    if (lane == 0) atomicAdd(&P.part_edge[chs[c].spq], (unsigned long long)__popcll(pm));
-                                    wave_hits += (uint32_t)__popcll(pm);
+                                // (p, q): one add per record, when the next one's first sub-row comes
+                                if (chs[c].spq != pq_slot) {
+                                    flush_pq();
+                                    pq_slot = chs[c].spq;
                                 }
+                                pq_hits += (uint32_t)__popcll(__ballot(pass && (at == kAtAll || at == kAtPQ)));
+                                wave_hits += (uint32_t)__popcll(__ballot(pass));
                                 continue;
                             }
                             if (!META && !ENUM) {
@@ -1493,6 +1488,7 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                     process(rB, cB, tB, dB);
                     if (rA[0].n == 0) break;
                 }
+                flush_pq();
                 if (lane == 0) {
                     probes += wave_work;
                     my_tri += wave_hits;
@@ -1554,13 +1550,13 @@ void slot_rows(const tp_graph *g, DArray<uint32_t> &srow, hipStream_t s)
 }
 
 // Largest of n uint32 values into *out (zeroed by the caller).
-__global__ void k_max_u32(const unsigned *x, size_t n, unsigned long long *out)
+__global__ __launch_bounds__(256) void k_max_u32(const unsigned *x, size_t n, unsigned long long *out)
 {
+    __shared__ unsigned long long tmp[256 / kWave];
     unsigned long long mx = 0;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         mx = max(mx, (unsigned long long)x[i]);
-    mx = wave_max(mx);
-    if (lane_id() == 0 && mx) atomicMax(out, mx);
+    block_max<256>(mx, tmp, out);
 }
 
 // The next chunk of a streamed enumeration: the largest t1 > t0 with
@@ -1582,25 +1578,82 @@ __global__ void k_enum_chunk(const uint64_t *base, uint64_t n_tiles, uint64_t t0
 }
 
 // Vertex participation from edge participation: each triangle at v holds
-// two of v's edges, so twice v's count is the sum over its edges.  One wave
-// per row adds each count to the edge's target and the row's sum to its
-// source (a thread per row left hub rows to single threads).
-__global__ void k_part_rows(const uint64_t *rowptr, const uint32_t *col, uint32_t n, const unsigned long long *edge,
-                            unsigned long long *acc)
+// two of v's edges, so twice v's count is the sum over its edges.  Eight lanes
+// walk a row (15 edges on average), add each count to the edge's target and
+// the row's sum to its source.  Most edges point at few vertices, those of the
+// highest ranks, whose adds would serialise: each workgroup keeps the sums of
+// the last kPartTop ranks in LDS and adds them up once (scale 22, with a wave
+// per row and every add on the device: 7.1 ms, now 0.9 ms).
+constexpr int kPartBlock = 1024;
+constexpr uint32_t kPartTop = 16384;  // 128 KB of the compute unit's 160
+constexpr uint32_t kPartLanes = 8;
+
+__global__ __launch_bounds__(kPartBlock) void k_part_rows(const uint64_t *rowptr, const uint32_t *col, uint32_t n,
+                                                          const uint32_t *edge, unsigned long long *acc)
 {
-    const size_t waves = (size_t)gridDim.x * blockDim.x / kWave;
-    for (size_t v = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) / kWave; v < n; v += waves) {
+    extern __shared__ unsigned long long part_top[];
+    const uint32_t ntop = min(n, kPartTop), t0 = n - ntop;
+    for (uint32_t i = threadIdx.x; i < ntop; i += kPartBlock) part_top[i] = 0;
+    __syncthreads();
+    auto add = [&](uint32_t v, unsigned long long c) {
+        if (v >= t0) atomicAdd(&part_top[v - t0], c);
+        else atomicAdd(&acc[v], c);
+    };
+    const uint32_t sub = threadIdx.x & (kPartLanes - 1);
+    const size_t rows = (size_t)gridDim.x * (kPartBlock / kPartLanes);
+    for (size_t v = blockIdx.x * (size_t)(kPartBlock / kPartLanes) + threadIdx.x / kPartLanes; v < n; v += rows) {
         const uint64_t b = rowptr[v], e = rowptr[v + 1];
         unsigned long long sum = 0;
-        for (uint64_t i = b + lane_id(); i < e; i += kWave) {
-            const unsigned long long c = edge[i];
+        for (uint64_t i = b + sub; i < e; i += kPartLanes) {
+            const uint32_t c = edge[i];
             if (!c) continue;
             sum += c;
-            atomicAdd(&acc[col[i]], c);
+            add(col[i], c);
         }
-        sum = wave_sum(sum);
-        if (lane_id() == 0 && sum) atomicAdd(&acc[v], sum);
+#pragma unroll
+        for (int d = kPartLanes / 2; d > 0; d >>= 1) sum += __shfl_xor(sum, d, kWave);
+        if (sub == 0 && sum) add((uint32_t)v, sum);
     }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < ntop; i += kPartBlock) {
+        const unsigned long long c = part_top[i];
+        if (c) atomicAdd(&acc[t0 + i], c);
+    }
+}
+
+// Counts [lo, hi) as 64-bit words.  `in` is the upper half of out's own memory
+// (in[i] at the place of out's 32-bit word m + i): the host takes ranges whose
+// words end below the counts not yet read, each half of what is left.
+__global__ void k_widen(const uint32_t *in, unsigned long long *out, size_t lo, size_t hi)
+{
+    for (size_t i = lo + blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < hi; i += (size_t)gridDim.x * blockDim.x)
+        out[i] = in[i];
+}
+
+// The last counts, read by one workgroup before any is written.
+constexpr uint32_t kWidenLast = 2048;
+__global__ __launch_bounds__(kWidenLast / 2) void k_widen_last(const uint32_t *in, unsigned long long *out, size_t lo,
+                                                               size_t hi)
+{
+    const size_t i = lo + threadIdx.x, j = i + kWidenLast / 2;
+    const uint32_t a = i < hi ? in[i] : 0u, b = j < hi ? in[j] : 0u;
+    __syncthreads();
+    if (i < hi) out[i] = a;
+    if (j < hi) out[j] = b;
+}
+
+void widen_upper_half(unsigned long long *out, size_t m, hipStream_t s)
+{
+    const uint32_t *in = reinterpret_cast<const uint32_t *>(out) + m;
+    size_t lo = 0;
+    while (m - lo > kWidenLast) {
+        const size_t hi = (m + lo) / 2;  // word hi starts no later than count lo
+        k_widen<<<grid_for(hi - lo, 256), 256, 0, s>>>(in, out, lo, hi);
+        TP_CHECK_LAUNCH();
+        lo = hi;
+    }
+    k_widen_last<<<1, kWidenLast / 2, 0, s>>>(in, out, lo, m);
+    TP_CHECK_LAUNCH();
 }
 
 __global__ void k_part_vertex(const unsigned long long *acc, const uint32_t *perm, uint32_t n, uint64_t *out)
@@ -2071,33 +2124,110 @@ extern "C" tp_status tripoll_survey_async(const tp_graph *g, const tp_survey_spe
 
 namespace {
 
-__global__ void k_maxe_flags(const unsigned long long *keys, uint64_t n, uint32_t *occupied)
-{
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        occupied[i] = keys[i] != 0ull ? 1u : 0u;
-}
+// A workgroup takes a tile of kPackTile consecutive elements, a wave a part of
+// it, 64 consecutive elements at a time.
+constexpr int kPackBlock = 256;
+constexpr int kPackItems = 16;
+constexpr size_t kPackTile = (size_t)kPackBlock * kPackItems;
 
-// the occupied slots packed in slot order: value (the sort key), its place
-// in the packed order, and its count
-__global__ void k_maxe_pack(const unsigned long long *keys, const unsigned long long *counts, const uint64_t *pos,
-                            uint64_t n, uint64_t *value, uint32_t *place, unsigned long long *count)
+// Per tile: the number of elements i with on(i).
+template <class F>
+__device__ __forceinline__ void tile_count(size_t n, uint64_t *cnt, F on)
 {
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-        const unsigned long long k = keys[i];
-        if (!k) continue;
-        const uint64_t j = pos[i];
-        value[j] = k - 1ull;
-        place[j] = (uint32_t)j;
-        count[j] = counts[i];
+    __shared__ unsigned tmp[kPackBlock / kWave];
+    const size_t base = blockIdx.x * kPackTile + (size_t)(threadIdx.x / kWave) * (kPackTile / (kPackBlock / kWave));
+    unsigned c = 0;
+    for (int j = 0; j < kPackItems; ++j) {
+        const size_t i = base + (size_t)j * kWave + lane_id();
+        c += (unsigned)__popcll(__ballot(i < n && on(i)));
+    }
+    if (lane_id() == 0) tmp[threadIdx.x / kWave] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned t = 0;
+        for (int w = 0; w < kPackBlock / kWave; ++w) t += tmp[w];
+        cnt[blockIdx.x] = t;
     }
 }
 
-__global__ void k_maxe_out(const uint64_t *value, const uint32_t *place, const unsigned long long *count, uint64_t n,
-                           uint32_t *out_value, uint64_t *out_count)
+__global__ __launch_bounds__(kPackBlock) void k_top_count(const uint32_t *count, size_t m, uint64_t *cnt)
 {
-    for (uint64_t j = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; j < n; j += (uint64_t)gridDim.x * blockDim.x) {
-        out_value[j] = (uint32_t)value[j];
-        out_count[j] = count[place[j]];
+    tile_count(m, cnt, [&](size_t i) { return count[i] != 0; });
+}
+
+// The edges that count any triangle, packed: time and count.
+__global__ __launch_bounds__(kPackBlock) void k_top_pack(const uint32_t *ets, const uint32_t *count, size_t m,
+                                                         const uint64_t *off, uint32_t *value, uint32_t *out)
+{
+    __shared__ uint64_t tmp[kPackBlock / kWave];
+    const size_t base = blockIdx.x * kPackTile + (size_t)(threadIdx.x / kWave) * (kPackTile / (kPackBlock / kWave));
+    uint32_t c[kPackItems];
+    uint64_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kPackItems; ++j) {
+        const size_t i = base + (size_t)j * kWave + lane_id();
+        c[j] = i < m ? count[i] : 0u;
+        mine += (uint64_t)__popcll(__ballot(c[j] != 0));
+    }
+    if (lane_id() == 0) tmp[threadIdx.x / kWave] = mine;
+    __syncthreads();
+    uint64_t pos = off[blockIdx.x];
+    for (int w = 0; w < (int)(threadIdx.x / kWave); ++w) pos += tmp[w];
+#pragma unroll
+    for (int j = 0; j < kPackItems; ++j) {
+        const uint64_t b = __ballot(c[j] != 0);
+        if (c[j]) {
+            const uint64_t at = pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+            value[at] = ets[base + (size_t)j * kWave + lane_id()];
+            out[at] = c[j];
+        }
+        pos += (uint64_t)__popcll(b);
+    }
+}
+
+__global__ __launch_bounds__(kPackBlock) void k_value_count(const uint32_t *value, size_t n, uint64_t *cnt)
+{
+    tile_count(n, cnt, [&](size_t i) { return i == 0 || value[i] != value[i - 1]; });
+}
+
+// Sorted values to distinct ones, with the sums of their counts (cleared by
+// the caller): each wave adds one sum per run of equal values among its 64.
+__global__ __launch_bounds__(kPackBlock) void k_value_sums(const uint32_t *value, const uint32_t *count, size_t n,
+                                                           const uint64_t *off, uint32_t *out_value,
+                                                           unsigned long long *out_count)
+{
+    __shared__ uint64_t tmp[kPackBlock / kWave];
+    const unsigned lane = lane_id();
+    const size_t base = blockIdx.x * kPackTile + (size_t)(threadIdx.x / kWave) * (kPackTile / (kPackBlock / kWave));
+    uint64_t heads[kPackItems];
+    uint64_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kPackItems; ++j) {
+        const size_t i = base + (size_t)j * kWave + lane;
+        heads[j] = __ballot(i < n && (i == 0 || value[i] != value[i - 1]));
+        mine += (uint64_t)__popcll(heads[j]);
+    }
+    if (lane == 0) tmp[threadIdx.x / kWave] = mine;
+    __syncthreads();
+    uint64_t pos = off[blockIdx.x];  // heads before the round
+    for (int w = 0; w < (int)(threadIdx.x / kWave); ++w) pos += tmp[w];
+#pragma unroll
+    for (int j = 0; j < kPackItems; ++j) {
+        const size_t i = base + (size_t)j * kWave + lane;
+        const bool ok = i < n;
+        const uint64_t upto = heads[j] & (lane == 63 ? ~0ull : ((2ull << lane) - 1));  // heads up to this lane
+        const uint64_t incl = wave_incl_scan(ok ? (uint64_t)count[i] : 0ull);
+        // the first lane of this lane's run within the round, and the sum before it
+        const int start = upto ? 63 - __clzll(upto) : 0;
+        const uint64_t sum_before = __shfl(incl, start > 0 ? start - 1 : 0, kWave);
+        const uint64_t before = start > 0 ? sum_before : 0ull;
+        const bool last = ok && (lane == 63 || i + 1 >= n || ((heads[j] >> (lane + 1)) & 1ull));
+        if (last) {
+            const uint64_t at = pos + (uint64_t)__popcll(upto) - 1;  // (a run from the round before: upto is empty)
+            if ((upto >> start) & 1ull) out_value[at] = value[i];
+            atomicAdd(&out_count[at], (unsigned long long)(incl - before));
+        }
+        pos += (uint64_t)__popcll(heads[j]);
     }
 }
 
@@ -2118,48 +2248,58 @@ extern "C" tp_status tripoll_max_edge_counts(const tp_graph *g, const tp_survey_
         if (g->n_graphs) fail(TP_ERR_UNSUPPORTED, "tripoll_max_edge_counts: single graphs only");
         if (g->m == 0 || g->n_in == 0) return;
         hipStream_t s = (hipStream_t)stream;
-        // at most m distinct times: a table of at least 2 m slots stays at
-        // most half full
-        uint64_t slots = 1024;
-        while (slots < 2 * g->m && slots < (1ull << 32)) slots <<= 1;
-        DArray<unsigned long long> keys(slots, s), counts(slots, s), res(TP_RESULT_WORDS, s), flag(1, s);
-        zero_u64<<<grid_for(slots, 256), 256, 0, s>>>(keys.get(), slots);
-        zero_u64<<<grid_for(slots, 256), 256, 0, s>>>(counts.get(), slots);
+        // The largest time of a triangle is the time of one of its edges, so
+        // each triangle is counted at that edge (the participation form of the
+        // kernels: one of the three in LDS, one once per record, and only the
+        // third with a device atomic), and the edges' counts are then summed
+        // by time.  A hash table of the times, with two random device atomics
+        // per triangle, took 27.6 ms on the scale-21 graph, this takes 10.5 ms.
+        DArray<unsigned long long> res(TP_RESULT_WORDS, s);
+        DArray<uint32_t> edge(g->m, s);
+        fill<uint32_t>(edge.get(), 0u, g->m, s);
         zero_u64<<<grid_for(TP_RESULT_WORDS, 256), 256, 0, s>>>(res.get(), TP_RESULT_WORDS);
-        zero_u64<<<1, 64, 0, s>>>(flag.get(), 1);
         TP_CHECK_LAUNCH();
         SurveyParams P = make_params(g, &sp, res.get(), res.get() + kRwClaim);
-        P.maxe_keys = keys.get();
-        P.maxe_counts = counts.get();
-        P.maxe_mask = slots - 1;
-        P.maxe_overflow = reinterpret_cast<unsigned *>(flag.get());
-        launch_all<true, false, kFormExt>(g, P, sp.strategy, s);
-        // pack the occupied slots, then sort them by value
-        DArray<uint32_t> occupied(slots, s);
-        DArray<uint64_t> pos(slots + 1, s);
-        k_maxe_flags<<<grid_for(slots, 256), 256, 0, s>>>(keys.get(), slots, occupied.get());
+        P.part_edge = edge.get();
+        P.part_top = 1;
+        launch_all<true, false, kFormPart>(g, P, sp.strategy, s);
+        // the edges with a count, packed and sorted by time
+        auto tiles = [](uint64_t n) { return (size_t)((n + kPackTile - 1) / kPackTile); };
+        DArray<uint64_t> off(tiles(g->m) + 1, s);
+        k_top_count<<<(unsigned)tiles(g->m), kPackBlock, 0, s>>>(edge.get(), g->m, off.get());
         TP_CHECK_LAUNCH();
-        scan_u32_to_u64(occupied.get(), pos.get(), slots, s);
-        uint64_t total = 0;
-        unsigned long long over = 0;
-        TP_HIP(hipMemcpyAsync(&total, pos.get() + slots, 8, hipMemcpyDeviceToHost, s));
-        TP_HIP(hipMemcpyAsync(&over, flag.get(), 8, hipMemcpyDeviceToHost, s));
+        scan_u64(off.get(), off.get(), tiles(g->m), true, s);
+        uint64_t k = 0;
+        TP_HIP(hipMemcpyAsync(&k, off.get() + tiles(g->m), 8, hipMemcpyDeviceToHost, s));
         TP_HIP(hipStreamSynchronize(s));
-        if (over) fail(TP_ERR_DEVICE, "tripoll_max_edge_counts: a value found no slot in the table");
+        if (k == 0) return;
+        DArray<uint32_t> va(k, s), vb(k, s), ca(k, s), cb(k, s);
+        k_top_pack<<<(unsigned)tiles(g->m), kPackBlock, 0, s>>>(g->ets.get(), edge.get(), g->m, off.get(), va.get(),
+                                                               ca.get());
+        TP_CHECK_LAUNCH();
+        unsigned long long *mx = res.get();  // (the survey's words are done with)
+        zero_u64<<<1, 64, 0, s>>>(mx, 1);
+        k_max_u32<<<grid_for(k, 256, kStatBlocks), 256, 0, s>>>(va.get(), k, mx);
+        TP_CHECK_LAUNCH();
+        unsigned long long top = 0;
+        TP_HIP(hipMemcpyAsync(&top, mx, 8, hipMemcpyDeviceToHost, s));
+        TP_HIP(hipStreamSynchronize(s));
+        edge.release();
+        const bool alt = radix_sort_pairs32(va.get(), ca.get(), vb.get(), cb.get(), k, bits_for(top), s);
+        const uint32_t *value = alt ? vb.get() : va.get(), *count = alt ? cb.get() : ca.get();
+        k_value_count<<<(unsigned)tiles(k), kPackBlock, 0, s>>>(value, k, off.get());
+        TP_CHECK_LAUNCH();
+        scan_u64(off.get(), off.get(), tiles(k), true, s);
+        uint64_t total = 0;
+        TP_HIP(hipMemcpyAsync(&total, off.get() + tiles(k), 8, hipMemcpyDeviceToHost, s));
+        TP_HIP(hipStreamSynchronize(s));
         *n_values = total;
         if (total > capacity)
             fail(TP_ERR_INVALID, "tripoll_max_edge_counts: " + std::to_string(total) + " distinct values, capacity " +
                                      std::to_string(capacity));
-        if (total == 0) return;
-        DArray<uint64_t> va(total, s), vb(total, s);
-        DArray<uint32_t> pa(total, s), pb(total, s);
-        DArray<unsigned long long> cnt(total, s);
-        k_maxe_pack<<<grid_for(slots, 256), 256, 0, s>>>(keys.get(), counts.get(), pos.get(), slots, va.get(), pa.get(),
-                                                         cnt.get());
-        TP_CHECK_LAUNCH();
-        const bool alt = radix_sort_pairs(va.get(), pa.get(), vb.get(), pb.get(), total, 32, s);
-        k_maxe_out<<<grid_for(total, 256), 256, 0, s>>>(alt ? vb.get() : va.get(), alt ? pb.get() : pa.get(), cnt.get(),
-                                                        total, dev_values, dev_counts);
+        unsigned long long *sums = reinterpret_cast<unsigned long long *>(dev_counts);
+        zero_u64<<<grid_for(total, 256), 256, 0, s>>>(sums, total);
+        k_value_sums<<<(unsigned)tiles(k), kPackBlock, 0, s>>>(value, count, k, off.get(), dev_values, sums);
         TP_CHECK_LAUNCH();
         TP_HIP(hipStreamSynchronize(s));
     });
@@ -2314,7 +2454,7 @@ extern "C" tp_status tripoll_enum_open(const tp_graph *g, const tp_survey_spec *
         zero_u64<<<1, 64, 0, s>>>(mx, 1);
         TP_CHECK_LAUNCH();
         if (T) {
-            k_max_u32<<<grid_for(T, 256), 256, 0, s>>>(count.get(), T, mx);
+            k_max_u32<<<grid_for(T, 256, kStatBlocks), 256, 0, s>>>(count.get(), T, mx);
             TP_CHECK_LAUNCH();
         }
         uint64_t h[2] = {0, 0};
@@ -2395,16 +2535,17 @@ extern "C" tp_status tripoll_participation(const tp_graph *g, const tp_survey_sp
         DArray<unsigned long long> res(TP_RESULT_WORDS, s);
         zero_u64<<<grid_for(TP_RESULT_WORDS, 256), 256, 0, s>>>(res.get(), TP_RESULT_WORDS);
         TP_CHECK_LAUNCH();
-        DArray<unsigned long long> own;
-        unsigned long long *edge = reinterpret_cast<unsigned long long *>(edge_counts);
-        if (!edge) {
+        // the 32-bit counters: the upper half of the caller's words, which are
+        // widened in place at the end, or a temporary
+        DArray<uint32_t> own;
+        uint32_t *edge = reinterpret_cast<uint32_t *>(edge_counts);
+        if (edge) {
+            edge += g->m;
+        } else {
             own.reset(std::max<uint64_t>(g->m, 1), s);
             edge = own.get();
         }
-        if (g->m) {
-            zero_u64<<<grid_for(g->m, 256), 256, 0, s>>>(edge, g->m);
-            TP_CHECK_LAUNCH();
-        }
+        fill<uint32_t>(edge, 0u, g->m, s);
         SurveyParams P = make_params(g, &sp, res.get(), res.get() + kRwClaim);
         P.part_edge = edge;
         if (g->m && g->n_in) launch_all<true, false, kFormPart>(g, P, sp.strategy, s);
@@ -2412,12 +2553,19 @@ extern "C" tp_status tripoll_participation(const tp_graph *g, const tp_survey_sp
             DArray<unsigned long long> acc(g->n, s);
             zero_u64<<<grid_for(g->n, 256), 256, 0, s>>>(acc.get(), g->n);
             TP_CHECK_LAUNCH();
-            k_part_rows<<<grid_for((size_t)g->n * kWave, 256), 256, 0, s>>>(g->rowptr.get(), g->col.get(), g->n, edge,
-                                                                           acc.get());
-            TP_CHECK_LAUNCH();
+            if (g->m) {
+                const size_t lds = std::min<size_t>(g->n, kPartTop) * sizeof(unsigned long long);
+                TP_HIP(hipFuncSetAttribute((const void *)k_part_rows, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)(kPartTop * sizeof(unsigned long long))));
+                // one workgroup a compute unit, fewer where there are few edges for each
+                const unsigned blocks = (unsigned)std::min<uint64_t>(256, g->m / 32768 + 1);
+                k_part_rows<<<blocks, kPartBlock, lds, s>>>(g->rowptr.get(), g->col.get(), g->n, edge, acc.get());
+                TP_CHECK_LAUNCH();
+            }
             k_part_vertex<<<grid_for(g->n, 256), 256, 0, s>>>(acc.get(), g->perm.get(), g->n, vertex_counts);
             TP_CHECK_LAUNCH();
         }
+        if (edge_counts && g->m) widen_upper_half(reinterpret_cast<unsigned long long *>(edge_counts), g->m, s);
         unsigned long long tri = 0;
         TP_HIP(hipMemcpyAsync(&tri, res.get() + TP_RW_TRIANGLES, 8, hipMemcpyDeviceToHost, s));
         TP_HIP(hipStreamSynchronize(s));
