@@ -263,12 +263,20 @@ void scan_u32_to_u64(const uint32_t *in, uint64_t *out, size_t n, hipStream_t s)
 
 namespace {
 
-constexpr int kSortBlock = 256;
-constexpr int kSortWaves = kSortBlock / kWave;
-constexpr int kSortRounds = 16;                           // keys per lane
-constexpr int kSortTile = kSortBlock * kSortRounds;       // 4096
+constexpr int kSortBlock = 256;  // threads of an upsweep block
 constexpr int kMaxRadixBits = 10;
 constexpr unsigned kMaxSortBlocks = 2048;
+
+// Shape of a downsweep tile: BLOCK threads of ROUNDS keys each.
+template <int BLOCK, int ROUNDS>
+struct SortShape {
+    static constexpr int kBlock = BLOCK;
+    static constexpr int kRounds = ROUNDS;
+    static constexpr int kWaves = BLOCK / kWave;
+    static constexpr int kTile = BLOCK * ROUNDS;
+};
+using SortNarrow = SortShape<256, 16>;
+using SortWide = SortShape<1024, 8>;
 
 template <int RB>
 __device__ __forceinline__ unsigned digit_of(uint64_t k, int shift)
@@ -277,16 +285,15 @@ __device__ __forceinline__ unsigned digit_of(uint64_t k, int shift)
 }
 
 template <class K, int RB>
-__global__ __launch_bounds__(kSortBlock) void radix_upsweep(const K *keys, size_t n, int shift,
-                                                            size_t tiles_per_block, uint64_t *hist)
+__global__ __launch_bounds__(kSortBlock) void radix_upsweep(const K *keys, size_t n, int shift, size_t chunk,
+                                                            uint64_t *hist)
 {
     constexpr int kRadix = 1 << RB;
     __shared__ unsigned cnt[kRadix];
     for (int d = threadIdx.x; d < kRadix; d += kSortBlock) cnt[d] = 0;
     __syncthreads();
-    const size_t t0 = blockIdx.x * tiles_per_block;
-    const size_t lo = t0 * kSortTile;
-    const size_t hi = std::min(n, (t0 + tiles_per_block) * kSortTile);
+    const size_t lo = blockIdx.x * chunk;
+    const size_t hi = std::min(n, lo + chunk);
     for (size_t i = lo + threadIdx.x; i < hi; i += kSortBlock) atomicAdd(&cnt[digit_of<RB>(keys[i], shift)], 1u);
     __syncthreads();
     for (int d = threadIdx.x; d < kRadix; d += kSortBlock) hist[(size_t)d * gridDim.x + blockIdx.x] = cnt[d];
@@ -294,19 +301,23 @@ __global__ __launch_bounds__(kSortBlock) void radix_upsweep(const K *keys, size_
 
 // K: uint64_t or uint32_t keys; VALS: whether 32-bit values travel with
 // them; RB: bits of the digit.
-template <class K, bool VALS, int RB>
-// (two blocks of 4 waves per compute unit: 10-bit digits with values need
-// all of 256 registers and 80 KB of LDS for it)
-__global__ __launch_bounds__(kSortBlock, 2) void radix_downsweep(const K *keys_in, const uint32_t *vals_in,
+template <class K, bool VALS, int RB, class S>
+// (the narrow shape: two blocks of 4 waves per compute unit, for which 10-bit
+// digits with values need all of 256 registers and 80 KB of LDS)
+__global__ __launch_bounds__(S::kBlock, S::kBlock == 256 ? 2 : 1) void radix_downsweep(const K *keys_in, const uint32_t *vals_in,
                                                               K *keys_out, uint32_t *vals_out, size_t n,
                                                               int shift, size_t tiles_per_block,
                                                               const uint64_t *offsets)
 {
     constexpr int kRadix = 1 << RB;
-    constexpr int kDigitsPerThread = kRadix / kSortBlock;
+    constexpr int kSortBlock = S::kBlock, kSortWaves = S::kWaves, kSortRounds = S::kRounds, kSortTile = S::kTile;
+    constexpr int kDigitsPerThread = kRadix > kSortBlock ? kRadix / kSortBlock : 1;
+    constexpr int kDigitThreads = kRadix / kDigitsPerThread;
     __shared__ K skey[kSortTile];
     __shared__ uint32_t sval[VALS ? kSortTile : 1];
-    __shared__ unsigned wcnt[kSortWaves][kRadix];  // per-wave running count, then per-wave base
+    // per-wave running count, then per-wave base within the digit (at most a
+    // tile's keys: 16 bits)
+    __shared__ uint16_t wcnt[kSortWaves][kRadix];
     __shared__ unsigned tstart[kRadix];
     __shared__ uint64_t grun[kRadix];              // next output position of each digit
     __shared__ unsigned scan_tmp[kSortWaves];
@@ -372,29 +383,35 @@ __global__ __launch_bounds__(kSortBlock, 2) void radix_downsweep(const K *keys_i
             }
             // the lowest lane of each digit group advances the running count;
             // same-wave LDS accesses are performed in program order
-            if (ok[r] && (peers & lt_mask) == 0) wcnt[w][dg[r]] = before + (unsigned)__popcll(peers);
+            if (ok[r] && (peers & lt_mask) == 0) wcnt[w][dg[r]] = (uint16_t)(before + (unsigned)__popcll(peers));
         }
         __syncthreads();
         // per-digit totals, wave bases and tile starts
         {
             unsigned loc[kDigitsPerThread];
             unsigned sum = 0;
+            const bool mine = kDigitThreads == kSortBlock || (int)threadIdx.x < kDigitThreads;
 #pragma unroll
             for (int j = 0; j < kDigitsPerThread; ++j) {
                 const unsigned d = threadIdx.x * kDigitsPerThread + j;
                 unsigned tot = 0;
-                for (int i = 0; i < kSortWaves; ++i) {
-                    const unsigned c = wcnt[i][d];
-                    wcnt[i][d] = tot;
-                    tot += c;
+                if (mine) {
+#pragma unroll
+                    for (int i = 0; i < kSortWaves; ++i) {
+                        const unsigned c = wcnt[i][d];
+                        wcnt[i][d] = (uint16_t)tot;
+                        tot += c;
+                    }
                 }
                 loc[j] = sum;
                 sum += tot;
             }
             unsigned total;
             const unsigned base = block_excl_scan<kSortBlock>(sum, scan_tmp, total);
+            if (mine) {
 #pragma unroll
-            for (int j = 0; j < kDigitsPerThread; ++j) tstart[threadIdx.x * kDigitsPerThread + j] = base + loc[j];
+                for (int j = 0; j < kDigitsPerThread; ++j) tstart[threadIdx.x * kDigitsPerThread + j] = base + loc[j];
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -426,26 +443,25 @@ __global__ __launch_bounds__(kSortBlock, 2) void radix_downsweep(const K *keys_i
 
 // One pass over digit [shift, shift + RB): histograms, their scan, the
 // stable scatter (values travel when vi is set).
-template <class K, int RB>
+template <class K, int RB, class S>
 void sort_pass(const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, size_t n, int shift, unsigned nb, size_t tpb,
                uint64_t *hist, hipStream_t s)
 {
-    radix_upsweep<K, RB><<<nb, kSortBlock, 0, s>>>(ki, n, shift, tpb, hist);
+    radix_upsweep<K, RB><<<nb, kSortBlock, 0, s>>>(ki, n, shift, tpb * S::kTile, hist);
     TP_CHECK_LAUNCH();
     scan_u64(hist, hist, (size_t)(1u << RB) * nb, false, s);
     if (vi)
-        radix_downsweep<K, true, RB><<<nb, kSortBlock, 0, s>>>(ki, vi, ko, vo, n, shift, tpb, hist);
+        radix_downsweep<K, true, RB, S><<<nb, S::kBlock, 0, s>>>(ki, vi, ko, vo, n, shift, tpb, hist);
     else
-        radix_downsweep<K, false, RB><<<nb, kSortBlock, 0, s>>>(ki, nullptr, ko, nullptr, n, shift, tpb, hist);
+        radix_downsweep<K, false, RB, S><<<nb, S::kBlock, 0, s>>>(ki, nullptr, ko, nullptr, n, shift, tpb, hist);
     TP_CHECK_LAUNCH();
 }
 
-template <class K>
-bool radix_sort(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, size_t n, int bits, hipStream_t s,
-                int begin_bit)
+template <class K, class S>
+bool radix_sort_shape(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, size_t n, int bits, hipStream_t s,
+                      int begin_bit)
 {
-    if (n <= 1 || bits <= 0) return false;
-    const size_t tiles = (n + kSortTile - 1) / kSortTile;
+    const size_t tiles = (n + S::kTile - 1) / S::kTile;
     const unsigned nb = (unsigned)std::min<size_t>(tiles, kMaxSortBlocks);
     const size_t tpb = (tiles + nb - 1) / nb;
     DArray<uint64_t> hist((size_t)(1u << kMaxRadixBits) * nb, s);
@@ -460,12 +476,31 @@ bool radix_sort(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, size_t
         const uint32_t *vi = in_alt ? vals_alt : vals;
         K *ko = in_alt ? keys : keys_alt;
         uint32_t *vo = in_alt ? vals : vals_alt;
-        if (pass < n10) sort_pass<K, 10>(ki, vi, ko, vo, n, shift, nb, tpb, hist.get(), s);
-        else sort_pass<K, 9>(ki, vi, ko, vo, n, shift, nb, tpb, hist.get(), s);
+        if (pass < n10) sort_pass<K, 10, S>(ki, vi, ko, vo, n, shift, nb, tpb, hist.get(), s);
+        else sort_pass<K, 9, S>(ki, vi, ko, vo, n, shift, nb, tpb, hist.get(), s);
         shift += pass < n10 ? 10 : 9;
         in_alt = !in_alt;
     }
     return in_alt;
+}
+
+// 64-bit keys from kWideKeys on take the wide shape's tiles of 8192 keys, one
+// per compute unit: a digit's keys of a tile fill whole lines of the output
+// (16 keys, 128 bytes, against 8), and half as many lines are open for writing
+// at a time (1.05e9 pairs: a 9-bit downsweep 7.46 -> 6.67 ms, 3.8 TB/s of reads
+// and writes where a copy reaches 4.6; 512 threads of 16 keys 6.70 ms; 64e6
+// pairs 535 -> 483 us).  32-bit keys alone move a third of the bytes and gain
+// more from a second block per compute unit (3.92 against 4.97 ms), and fewer
+// keys than that leave compute units without a tile.
+constexpr size_t kWideKeys = size_t(1) << 22;
+
+template <class K>
+bool radix_sort(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, size_t n, int bits, hipStream_t s,
+                int begin_bit)
+{
+    if (n <= 1 || bits <= 0) return false;
+    if (sizeof(K) == 8 && n >= kWideKeys) return radix_sort_shape<K, SortWide>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
+    return radix_sort_shape<K, SortNarrow>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
 }
 
 }  // namespace
