@@ -159,9 +159,13 @@ __device__ __forceinline__ uint64_t wave_heads(const uint64_t *keys, size_t n, s
     return c;
 }
 
-__global__ __launch_bounds__(kB) void k_dedup_count(const uint64_t *keys, size_t n, int dbit, uint64_t *tile_cnt)
+// (The self-loops, at the end of the M sorted keys, are counted on the device
+// and left out.)
+__global__ __launch_bounds__(kB) void k_dedup_count(const uint64_t *keys, const unsigned long long *loops, size_t M,
+                                                    int dbit, uint64_t *tile_cnt)
 {
     __shared__ uint64_t tmp[kB / kWave];
+    const size_t n = M - (size_t)*loops;
     const int w = threadIdx.x / kWave;
     const uint64_t c = wave_heads(keys, n, blockIdx.x * kCompTile + (size_t)w * kCompWave, dbit);
     if (lane_id() == 0) tmp[w] = c;
@@ -184,25 +188,36 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
 
 // One pair per run with its earliest time; with direction bits (dbit = 1)
 // also the directions of its copies (bit 0: lower -> higher id, bit 1: the
-// reverse) into udir.  The wave keeps its 16 rounds of keys in registers
-// from the count of its heads: the neighbours a head compares with come
-// from the lanes beside it (or the next round's first lane), and only a run
-// of copies is walked in memory.
-__global__ __launch_bounds__(kB) void k_dedup_write(const uint64_t *keys, const uint32_t *vals, size_t n, int dbit,
+// reverse) into udir.  The wave keeps its 16 rounds of keys and times in
+// registers and reduces the runs of a round by shuffles, as many steps as its
+// longest run needs (few rounds of a large graph hold a run above 2); a run
+// that goes on is carried from the round after it, and past the wave's part
+// it is walked by the whole wave.  (Walked copy by copy by its head's lane, the
+// 100 copies of a small graph's hub pair took 86 of its build's 1200 us, now
+// 14.)
+__global__ __launch_bounds__(kB) void k_dedup_write(const uint64_t *keys, const uint32_t *vals,
+                                                    const unsigned long long *loops, size_t M, int dbit,
                                                     const uint64_t *tile_off, uint64_t *ukey, uint32_t *uts,
                                                     uint8_t *udir)
 {
     __shared__ uint64_t tmp[kB / kWave];
+    const size_t n = M - (size_t)*loops;
     const int w = threadIdx.x / kWave;
     const unsigned lane = lane_id();
     const size_t wbase = blockIdx.x * kCompTile + (size_t)w * kCompWave;
     uint64_t kk[kCompItems];
     uint64_t hm[kCompItems];  // each round's heads
+    uint32_t tt[kCompItems];
     uint64_t c = 0;
 #pragma unroll
     for (int j = 0; j < kCompItems; ++j) {
         const size_t i = wbase + (size_t)j * kWave + lane;
         kk[j] = i < n ? keys[i] : 0ull;
+        tt[j] = i < n ? vals[i] : 0xffffffffu;
+    }
+#pragma unroll
+    for (int j = 0; j < kCompItems; ++j) {
+        const size_t i = wbase + (size_t)j * kWave + lane;
         uint64_t prev = __shfl_up(kk[j], 1, kWave);
         if (j > 0) {
             const uint64_t last = readlane64(kk[j - 1], kWave - 1);
@@ -215,38 +230,69 @@ __global__ __launch_bounds__(kB) void k_dedup_write(const uint64_t *keys, const 
     }
     if (lane == 0) tmp[w] = c;
     __syncthreads();
-    uint64_t pos = tile_off[blockIdx.x];
+    uint64_t pos = tile_off[blockIdx.x] + c;  // past this wave's heads
     for (int x = 0; x < w; ++x) pos += tmp[x];
-#pragma unroll
-    for (int j = 0; j < kCompItems; ++j) {
-        const size_t i = wbase + (size_t)j * kWave + lane;
-        const uint64_t k = kk[j];
-        // the key after this one: the next lane's, the next round's first, or memory
-        uint64_t next = __shfl_down(k, 1, kWave);
-        if (j + 1 < kCompItems) {
-            const uint64_t first = readlane64(kk[j + 1], 0);
-            if (lane == kWave - 1) next = first;
-        } else if (lane == kWave - 1) {
-            next = i + 1 < n ? keys[i + 1] : 0ull;
-        }
-        const uint64_t b = hm[j];
-        if ((b >> lane) & 1ull) {
-            // the earliest time of the run, and its directions
-            const uint64_t pk = k >> dbit;
-            uint32_t t = vals[i];
-            uint32_t d = 1u << (k & (uint64_t)dbit);
-            if (i + 1 < n && (next >> dbit) == pk) {
-                for (size_t x = i + 1; x < n && (keys[x] >> dbit) == pk; ++x) {
-                    t = min(t, vals[x]);
-                    d |= 1u << (keys[x] & (uint64_t)dbit);
-                }
+    if (c == 0) return;
+    // the part of the wave's last run past its part
+    uint32_t carry_t = 0xffffffffu, carry_d = 0;
+    const size_t wend = wbase + kCompWave;
+    if (wend < n) {
+        const uint64_t pk = readlane64(kk[kCompItems - 1], kWave - 1) >> dbit;
+        for (size_t b = wend;; b += kWave) {
+            const size_t x = b + lane;
+            const uint64_t k = x < n ? keys[x] : 0ull;
+            const bool same = x < n && (k >> dbit) == pk;
+            if (same) {
+                carry_t = min(carry_t, vals[x]);
+                carry_d |= 1u << (k & (uint64_t)dbit);
             }
+            if (__ballot(same) != ~0ull) break;
+        }
+#pragma unroll
+        for (int d = kWave / 2; d > 0; d >>= 1) {
+            carry_t = min(carry_t, (uint32_t)__shfl_xor(carry_t, d, kWave));
+            carry_d |= (uint32_t)__shfl_xor(carry_d, d, kWave);
+        }
+    }
+    // rounds from the last to the first
+#pragma unroll
+    for (int j = kCompItems - 1; j >= 0; --j) {
+        const size_t base = wbase + (size_t)j * kWave;
+        if (base >= n) continue;
+        const uint32_t valid = (uint32_t)min((size_t)kWave, n - base);
+        const uint64_t k = kk[j], b = hm[j];
+        uint32_t t = tt[j];
+        uint32_t d = lane < valid ? 1u << (k & (uint64_t)dbit) : 0u;
+        // lanes after this one in its run, in this round
+        const uint64_t above = lane == kWave - 1 ? 0ull : (b & (~0ull << (lane + 1)));
+        const uint32_t end = above ? (uint32_t)__ffsll((long long)above) - 1 : valid;
+        const uint32_t rest = lane < valid ? end - lane - 1 : 0u;
+        for (uint32_t step = 1; __ballot(rest >= step); step <<= 1) {
+            const uint32_t ot = __shfl_down(t, step, kWave);
+            if (rest >= step) t = min(t, ot);
+            if (udir) {
+                const uint32_t od = __shfl_down(d, step, kWave);
+                if (rest >= step) d |= od;
+            }
+        }
+        // the round's last run goes on after it
+        if (end == valid) {
+            t = min(t, carry_t);
+            d |= carry_d;
+        }
+        pos -= (uint64_t)__popcll(b);
+        if ((b >> lane) & 1ull) {
             const uint64_t at = pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-            ukey[at] = pk;
+            ukey[at] = k >> dbit;
             uts[at] = t;
             if (udir) udir[at] = (uint8_t)d;
         }
-        pos += (uint64_t)__popcll(b);
+        // carried into the round before: this round's first run, unless it
+        // starts here
+        const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)t, 0);
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, 0);
+        carry_t = (b & 1ull) ? 0xffffffffu : t0;
+        carry_d = (b & 1ull) ? 0u : d0;
     }
 }
 
@@ -296,14 +342,18 @@ __global__ void k_degree_runs(const uint32_t *v, size_t m, uint32_t *deg)
     }
 }
 
-template <class T>
-__global__ __launch_bounds__(kB) void k_max(const T *x, size_t n, unsigned long long *out)
+// The largest degree and the largest label (vlab null: 0).
+__global__ __launch_bounds__(kB) void k_vertex_max(const uint32_t *deg, const uint8_t *vlab, size_t n,
+                                                   unsigned long long *dmax, unsigned long long *lmax)
 {
     __shared__ unsigned long long tmp[kB / kWave];
-    unsigned long long mx = 0;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        mx = max(mx, (unsigned long long)x[i]);
-    block_max<kB>(mx, tmp, out);
+    uint32_t d = 0, l = 0;
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        d = max(d, deg[i]);
+        if (vlab) l = max(l, (uint32_t)vlab[i]);
+    }
+    block_max<kB>(d, tmp, dmax);
+    block_max<kB>(l, tmp, lmax);
 }
 
 // A bijection of [0, 2^nb): xor-shifts and odd multiplications modulo 2^nb.
@@ -441,10 +491,18 @@ __global__ void k_orient(const uint64_t *ukey, const uint8_t *udir, size_t m, Pa
 // of them writes each slot's target, its label, its source and (directed
 // builds) the two direction bits below the pair into edir, and counts d+(s):
 // each wave adds one count per run of equal sources among its 64 pairs, to
-// increasing addresses.
-__global__ void k_csr(const uint64_t *okey, size_t m, PairCode pc, const uint8_t *rlab, uint32_t *col, uint8_t *tlab,
-                      uint32_t *srow, uint8_t *edir, uint32_t *dplus)
+// increasing addresses.  The first block clears the pads of col, ets and edir.
+__global__ void k_csr(const uint64_t *okey, size_t m, PairCode pc, const uint8_t *rlab, uint32_t *col, uint32_t *ets,
+                      uint8_t *tlab, uint32_t *srow, uint8_t *edir, uint32_t *dplus)
 {
+    if (blockIdx.x == 0) {
+        for (uint32_t i = threadIdx.x; i < kRowPad; i += blockDim.x) {
+            col[m + i] = 0;
+            ets[m + i] = 0;
+        }
+        if (edir)
+            for (uint32_t i = threadIdx.x; i < 4 * kRowPad; i += blockDim.x) edir[m + i] = 0;
+    }
     const int dshift = edir ? 2 : 0;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t base = blockIdx.x * (size_t)blockDim.x + (threadIdx.x & ~(kWave - 1)); base < m; base += stride) {
@@ -584,19 +642,22 @@ __device__ __forceinline__ uint32_t tiles_of(uint64_t cnt, uint64_t work, uint32
 }
 
 // The caps of the work tiles (the cut the surveys walk): where a class has
-// too little work to give every claimer of a full device about
-// kShare tiles at the plan's cap, its records are cut finer, down to a floor
+// too little work to give every claimer of a full device about 8 tiles (4 in
+// the larger two classes) at the plan's cap, its records are cut finer, down to a floor
 // below which a tile's table and claim would outweigh its records.  The
 // claimers are waves for the tiny class and workgroups for the others, as
 // many as 256 compute units hold (32 waves, 5 and 1 workgroups each).  Without
 // it a small graph waits for the one wave or workgroup that walks its largest
 // target (scale 13: 1024 records on one wave, 247 us of a 380 us survey).
+// 8 tiles against 4: 300-graph batch's tiny class 1.63 against 2.07 ms, 300,007
+// vertices' small class 407 against 467 us, scale 22's large class 2.71
+// against 2.63 ms.
 __device__ __forceinline__ uint32_t work_rec_cap(int c, uint32_t rec_cap, uint64_t class_records)
 {
-    constexpr uint64_t kShare = 4;
+    const uint64_t share = c == kClassTiny || c == kClassSmall ? 8 : 4;
     const uint64_t claimers = c == kClassTiny ? 256 * 32 : (c == kClassSmall ? 256 * 5 : 256);
-    const uint32_t least = c == kClassTiny || c == kClassSmall ? kWorkRecMin : kWorkRecMinLarge;
-    const uint64_t want = class_records / (claimers * kShare);
+    const uint32_t least = c == kClassTiny ? kWorkRecMinTiny : (c == kClassSmall ? kWorkRecMinSmall : kWorkRecMinLarge);
+    const uint64_t want = class_records / (claimers * share);
     return (uint32_t)min((uint64_t)rec_cap, max((uint64_t)least, want));
 }
 
@@ -952,6 +1013,7 @@ uint64_t graph_bytes(const tp_graph *g)
 // recomputed from the in-edge index.
 void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
 {
+    CallScope scope(s);
     const uint32_t n = g->n;
     DArray<unsigned long long> work(n, s);
     DArray<uint64_t> cptr((size_t)n + 1, s);
@@ -1083,6 +1145,7 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
     if (el->n_edges > 0 && (!el->src || !el->dst)) fail(TP_ERR_INVALID, "tripoll_build: NULL src/dst");
     if (el->flags & ~TP_EDGES_DIRECTED) fail(TP_ERR_INVALID, "tripoll_build: unknown flags");
 
+    CallScope scope(s);  // temporaries of the build are reused without waiting
     const uint32_t n = el->n_vertices;
     const size_t M = el->n_edges;
     const int nb = std::max(1, bits_for((uint64_t)n - 1));
@@ -1130,11 +1193,11 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
     const uint32_t *ts = to_device(el->edge_time, M, el->mem_space, h_ts, s);
     const uint8_t *vlab = to_device(el->vertex_label, n, el->mem_space, h_lab, s);
 
-    // bad ids, self-loops, d_max, max label, wedges, d+_max, probes, active targets
+    // bad ids, self-loops, d_max, max label, wedges, d+_max, in-edge records
     DArray<unsigned long long> counters(8, s);
     TP_HIP(hipMemsetAsync(counters.get(), 0, 8 * sizeof(unsigned long long), s));
     unsigned long long *c_bad = counters.get(), *c_loop = c_bad + 1, *c_dmax = c_bad + 2, *c_lab = c_bad + 3,
-                       *c_wedge = c_bad + 4, *c_dpmax = c_bad + 5;
+                       *c_wedge = c_bad + 4, *c_dpmax = c_bad + 5, *c_kept = c_bad + 6;
 
     const size_t Mcap = std::max<size_t>(M, 1);
     DArray<uint64_t> keyA(Mcap, s), keyB(Mcap, s);
@@ -1161,16 +1224,9 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
                                       per_block);
         TP_CHECK_LAUNCH();
     }
-    unsigned long long hc[2];
-    TP_HIP(hipMemcpyAsync(hc, counters.get(), 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    TP_HIP(hipStreamSynchronize(s));
-    if (hc[0]) fail(TP_ERR_INVALID, "tripoll_build: " + std::to_string(hc[0]) + " edge endpoints >= n_vertices");
     h_src.release();
     h_dst.release();
     h_ts.release();
-    const size_t Mv = M - (size_t)hc[1];  // edges that are not self-loops
-    g->stats.n_raw_edges = M;
-    g->stats.n_self_loops = hc[1];
     TP_HIP(hipEventRecord(ev[1], s));
 
     // ---- phase 1: sort by pair
@@ -1186,18 +1242,23 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
     DArray<uint8_t> udir;
     if (directed) udir.reset(Mcap, s);
     {
-        const size_t nt = std::max<size_t>(1, (Mv + kCompTile - 1) / kCompTile);
+        const size_t nt = std::max<size_t>(1, (M + kCompTile - 1) / kCompTile);
         DArray<uint64_t> toff(nt + 1, s);
-        if (Mv) {
-            k_dedup_count<<<(unsigned)nt, kB, 0, s>>>(skey, Mv, dbit, toff.get());
+        if (M) {
+            k_dedup_count<<<(unsigned)nt, kB, 0, s>>>(skey, c_loop, M, dbit, toff.get());
             TP_CHECK_LAUNCH();
         } else {
             TP_HIP(hipMemsetAsync(toff.get(), 0, sizeof(uint64_t), s));
         }
         scan_u64(toff.get(), toff.get(), nt, true, s);
+        unsigned long long hc[2];
+        TP_HIP(hipMemcpyAsync(hc, counters.get(), sizeof(hc), hipMemcpyDeviceToHost, s));
         m = read_scalar(toff.get() + nt, s);
-        if (Mv) {
-            k_dedup_write<<<(unsigned)nt, kB, 0, s>>>(skey, sval, Mv, dbit, toff.get(), fkey, fval, udir.get());
+        if (hc[0]) fail(TP_ERR_INVALID, "tripoll_build: " + std::to_string(hc[0]) + " edge endpoints >= n_vertices");
+        g->stats.n_raw_edges = M;
+        g->stats.n_self_loops = hc[1];
+        if (m) {
+            k_dedup_write<<<(unsigned)nt, kB, 0, s>>>(skey, sval, c_loop, M, dbit, toff.get(), fkey, fval, udir.get());
             TP_CHECK_LAUNCH();
         }
     }
@@ -1222,12 +1283,8 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
             k_degree_runs<<<grid_for(m, kB), kB, 0, s>>>(hb2 ? hiB : hiA, m, deg.get());
             TP_CHECK_LAUNCH();
         }
-        k_max<uint32_t><<<grid_for(n, kB, kStatBlocks), kB, 0, s>>>(deg.get(), n, c_dmax);
+        k_vertex_max<<<grid_for(n, kB, kStatBlocks), kB, 0, s>>>(deg.get(), vlab, n, c_dmax, c_lab);
         TP_CHECK_LAUNCH();
-        if (vlab) {
-            k_max<uint8_t><<<grid_for(n, kB, kStatBlocks), kB, 0, s>>>(vlab, n, c_lab);
-            TP_CHECK_LAUNCH();
-        }
         unsigned long long mx[2];
         TP_HIP(hipMemcpyAsync(mx, c_dmax, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
         TP_HIP(hipStreamSynchronize(s));
@@ -1294,19 +1351,14 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
     g->col.reset(m + kRowPad, s);
     g->tlab.reset(std::max<uint64_t>(m, 1), s);
     g->ets = std::move(ots == valA.get() ? valA : valB);
-    TP_HIP(hipMemsetAsync(g->col.get() + m, 0, kRowPad * sizeof(uint32_t), s));
-    TP_HIP(hipMemsetAsync(g->ets.get() + m, 0, kRowPad * sizeof(uint32_t), s));
     if (directed) {
         g->directed = true;
         g->edir.reset(m + kRowPad * 4, s);
-        TP_HIP(hipMemsetAsync(g->edir.get() + m, 0, kRowPad * 4, s));
     }
     uint32_t *srow = spare_val;
-    if (m) {
-        k_csr<<<grid_for(m, kB), kB, 0, s>>>(okey, m, pc, g->rlab.get(), g->col.get(), g->tlab.get(), srow,
-                                             g->edir.get(), dplus.get());
-        TP_CHECK_LAUNCH();
-    }
+    k_csr<<<grid_for(m, kB), kB, 0, s>>>(okey, m, pc, g->rlab.get(), g->col.get(), g->ets.get(), g->tlab.get(), srow,
+                                         g->edir.get(), dplus.get());
+    TP_CHECK_LAUNCH();
     g->rowptr.reset((size_t)n + 1, s);
     scan_u32_to_u64(dplus.get(), g->rowptr.get(), n, s);
     dplus.release();
@@ -1330,18 +1382,15 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
         // ets); srow's buffer is free once the keys are written
         DArray<uint32_t> pay(std::max<uint64_t>(m, 1), s);
         uint32_t *ival = pay.get(), *ival_alt = srow;
-        DArray<unsigned long long> kept(1, s);
-        TP_HIP(hipMemsetAsync(kept.get(), 0, sizeof(unsigned long long), s));
         DArray<uint64_t> has_out;
         if (m) {
             has_out.reset((n + 63) / 64, s);
             k_has_out<<<grid_for(n, kB), kB, 0, s>>>(g->rowptr.get(), n, has_out.get());
             TP_CHECK_LAUNCH();
             k_in_keys<<<grid_for(m, kB, kStatBlocks), kB, 0, s>>>(srow, g->col.get(), g->rowptr.get(), has_out.get(),
-                                                     g->rlab.get(), m, kbits, n, ikey, ival, kept.get());
+                                                     g->rlab.get(), m, kbits, n, ikey, ival, c_kept);
             TP_CHECK_LAUNCH();
         }
-        g->n_in = read_scalar(kept.get(), s);
         const bool alt = radix_sort_pairs(ikey, ival, ikey_alt, ival_alt, m, nb + 1, s, kbits);
         if (alt) {
             std::swap(ikey, ikey_alt);
@@ -1362,16 +1411,17 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
     // ---- phase 7: work per target and the tile plan per class
     PlanCfg cfg{};
     for (int c = 0; c < kNumClasses; ++c) cfg.tile_records[c] = default_tile_records(c);
-    g->stats.dplus_max = read_scalar(c_dpmax, s);  // the plan cuts huge targets' records
+    unsigned long long hs[8];
+    TP_HIP(hipMemcpyAsync(hs, counters.get(), sizeof(hs), hipMemcpyDeviceToHost, s));
+    TP_HIP(hipStreamSynchronize(s));
+    g->n_in = hs[6];
+    g->stats.dplus_max = hs[5];  // the plan cuts huge targets' records
     plan_graph(g.get(), cfg, s);
     TP_HIP(hipEventRecord(ev[8], s));
     TP_HIP(hipStreamSynchronize(s));
 
-    unsigned long long hs[8];
-    TP_HIP(hipMemcpy(hs, counters.get(), 8 * sizeof(unsigned long long), hipMemcpyDeviceToHost));
     g->stats.n_vertices = n;
     g->stats.wedges = hs[4];
-    g->stats.dplus_max = hs[5];
     // the survey packs a position in Adj+(q) into 22 bits; d+ <= sqrt(2m) keeps
     // this far away for any graph that fits in memory
     if (hs[5] >= (1ull << 22)) fail(TP_ERR_UNSUPPORTED, "tripoll_build: out-degree above 2^22 in the oriented graph");

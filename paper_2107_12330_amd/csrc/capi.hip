@@ -24,8 +24,12 @@ extern "C" tp_status tripoll_graph_free(tp_graph *g)
         int cur = 0;
         TP_HIP(hipGetDevice(&cur));
         if (cur != g->device) TP_HIP(hipSetDevice(g->device));
-        delete g;
-        if (cur != g->device) TP_HIP(hipSetDevice(cur));
+        const int dev = g->device;
+        {
+            CallScope scope(g->rowptr.s);  // one wait for all of its arrays
+            delete g;
+        }
+        if (cur != dev) TP_HIP(hipSetDevice(cur));
     });
 }
 

@@ -64,7 +64,56 @@ std::atomic<uint64_t> g_fail_countdown{0};
 
 void dev_fail_after(uint64_t n) { g_fail_countdown.store(n); }
 
-void *dev_alloc(size_t bytes)
+// ---- the calling thread's scope
+
+namespace {
+
+struct Scope {
+    bool on = false;
+    hipStream_t stream = nullptr;
+    std::multimap<size_t, void *> blocks;  // released in the scope, by size; still live in the pool
+};
+thread_local Scope t_scope;
+
+// A cached block may stand in for a request that is not much smaller.
+bool fits(size_t block, size_t sz) { return block <= sz + sz / 4 + (size_t(8) << 20); }
+
+// Wait for the scope's stream and hand its blocks to the pool's cache.
+void scope_flush(Scope &sc)
+{
+    if (sc.blocks.empty()) return;
+    (void)hipStreamSynchronize(sc.stream);
+    Pool &p = pool_for_current_device();
+    std::lock_guard<std::mutex> lk(p.mu);
+    for (auto &kv : sc.blocks) {
+        if (!p.live.erase(kv.second)) continue;
+        p.free_blocks.emplace(kv.first, kv.second);
+        p.cached += kv.first;
+    }
+    sc.blocks.clear();
+}
+
+}  // namespace
+
+CallScope::CallScope(hipStream_t stream) : outer_(!t_scope.on)
+{
+    if (!outer_) return;
+    t_scope.on = true;
+    t_scope.stream = stream;
+}
+
+CallScope::~CallScope()
+{
+    if (!outer_) return;
+    t_scope.on = false;
+    try {
+        scope_flush(t_scope);
+    } catch (...) {
+        t_scope.blocks.clear();  // no current device: the blocks stay counted as live
+    }
+}
+
+void *dev_alloc(size_t bytes, hipStream_t stream)
 {
     for (uint64_t c = g_fail_countdown.load(); c;) {
         if (g_fail_countdown.compare_exchange_weak(c, c - 1)) {
@@ -74,10 +123,18 @@ void *dev_alloc(size_t bytes)
     }
     Pool &p = pool_for_current_device();
     const size_t sz = round_size(bytes ? bytes : 1);
-    std::lock_guard<std::mutex> lk(p.mu);
+    if (t_scope.on && stream == t_scope.stream) {
+        auto own = t_scope.blocks.lower_bound(sz);
+        if (own != t_scope.blocks.end() && fits(own->first, sz)) {
+            void *ptr = own->second;
+            t_scope.blocks.erase(own);
+            return ptr;
+        }
+    }
+    std::unique_lock<std::mutex> lk(p.mu);
     auto it = p.free_blocks.lower_bound(sz);
     // reuse a cached block when it is not much larger than the request
-    if (it != p.free_blocks.end() && it->first <= sz + sz / 4 + (size_t(8) << 20)) {
+    if (it != p.free_blocks.end() && fits(it->first, sz)) {
         void *ptr = it->second;
         p.live[ptr] = it->first;
         p.cached -= it->first;
@@ -88,6 +145,11 @@ void *dev_alloc(size_t bytes)
     hipError_t e = hipMalloc(&ptr, sz);
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
         (void)hipGetLastError();
+        if (t_scope.on) {
+            lk.unlock();
+            scope_flush(t_scope);
+            lk.lock();
+        }
         trim_locked(p);
         e = hipMalloc(&ptr, sz);
     }
@@ -103,9 +165,15 @@ void *dev_alloc(size_t bytes)
 void dev_release(void *ptr, hipStream_t stream)
 {
     if (!ptr) return;
+    Pool &p = pool_for_current_device();
+    if (t_scope.on && stream == t_scope.stream) {
+        std::lock_guard<std::mutex> lk(p.mu);
+        auto it = p.live.find(ptr);
+        if (it != p.live.end()) t_scope.blocks.emplace(it->second, ptr);
+        return;
+    }
     // the block may still be in use by work on `stream`
     (void)hipStreamSynchronize(stream);
-    Pool &p = pool_for_current_device();
     std::lock_guard<std::mutex> lk(p.mu);
     auto it = p.live.find(ptr);
     if (it == p.live.end()) return;
@@ -275,6 +343,7 @@ struct SortShape {
     static constexpr int kWaves = BLOCK / kWave;
     static constexpr int kTile = BLOCK * ROUNDS;
 };
+using SortSmall = SortShape<256, 4>;
 using SortNarrow = SortShape<256, 16>;
 using SortWide = SortShape<1024, 8>;
 
@@ -284,7 +353,9 @@ __device__ __forceinline__ unsigned digit_of(uint64_t k, int shift)
     return (unsigned)(k >> shift) & ((1u << RB) - 1);
 }
 
-template <class K, int RB>
+// FEW: at most kFewBlocks blocks, whose counts leave as 32-bit words block by
+// block, for the downsweep to add up itself.
+template <class K, int RB, bool FEW>
 __global__ __launch_bounds__(kSortBlock) void radix_upsweep(const K *keys, size_t n, int shift, size_t chunk,
                                                             uint64_t *hist)
 {
@@ -296,15 +367,20 @@ __global__ __launch_bounds__(kSortBlock) void radix_upsweep(const K *keys, size_
     const size_t hi = std::min(n, lo + chunk);
     for (size_t i = lo + threadIdx.x; i < hi; i += kSortBlock) atomicAdd(&cnt[digit_of<RB>(keys[i], shift)], 1u);
     __syncthreads();
-    for (int d = threadIdx.x; d < kRadix; d += kSortBlock) hist[(size_t)d * gridDim.x + blockIdx.x] = cnt[d];
+    if (FEW) {
+        uint32_t *few = reinterpret_cast<uint32_t *>(hist) + (size_t)blockIdx.x * kRadix;
+        for (int d = threadIdx.x; d < kRadix; d += kSortBlock) few[d] = cnt[d];
+    } else {
+        for (int d = threadIdx.x; d < kRadix; d += kSortBlock) hist[(size_t)d * gridDim.x + blockIdx.x] = cnt[d];
+    }
 }
 
 // K: uint64_t or uint32_t keys; VALS: whether 32-bit values travel with
 // them; RB: bits of the digit.
-template <class K, bool VALS, int RB, class S>
+template <class K, bool VALS, int RB, class S, bool FEW>
 // (the narrow shape: two blocks of 4 waves per compute unit, for which 10-bit
 // digits with values need all of 256 registers and 80 KB of LDS)
-__global__ __launch_bounds__(S::kBlock, S::kBlock == 256 ? 2 : 1) void radix_downsweep(const K *keys_in, const uint32_t *vals_in,
+__global__ __launch_bounds__(S::kBlock, S::kRounds == 16 ? 2 : 1) void radix_downsweep(const K *keys_in, const uint32_t *vals_in,
                                                               K *keys_out, uint32_t *vals_out, size_t n,
                                                               int shift, size_t tiles_per_block,
                                                               const uint64_t *offsets)
@@ -326,8 +402,39 @@ __global__ __launch_bounds__(S::kBlock, S::kBlock == 256 ? 2 : 1) void radix_dow
     const unsigned lane = lane_id();
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
+    if (FEW) {
+        // the digit's first place: all smaller digits, then this one in the
+        // blocks before
+        const uint32_t *few = reinterpret_cast<const uint32_t *>(offsets);
+        unsigned before[kDigitsPerThread], all[kDigitsPerThread], sum = 0;
+        const bool mine = kDigitThreads == kSortBlock || (int)threadIdx.x < kDigitThreads;
+#pragma unroll
+        for (int j = 0; j < kDigitsPerThread; ++j) before[j] = all[j] = 0;
+        if (mine) {
+#pragma unroll 8
+            for (unsigned b = 0; b < gridDim.x; ++b) {
+#pragma unroll
+                for (int j = 0; j < kDigitsPerThread; ++j) {
+                    const unsigned c = few[(size_t)b * kRadix + threadIdx.x * kDigitsPerThread + j];
+                    before[j] += b < blockIdx.x ? c : 0u;
+                    all[j] += c;
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kDigitsPerThread; ++j) sum += all[j];
+        unsigned total;
+        unsigned at = block_excl_scan<kSortBlock>(sum, scan_tmp, total);
+        if (mine) {
+#pragma unroll
+            for (int j = 0; j < kDigitsPerThread; ++j) {
+                grun[threadIdx.x * kDigitsPerThread + j] = at + before[j];
+                at += all[j];
+            }
+        }
+    }
     for (int d = threadIdx.x; d < kRadix; d += kSortBlock) {
-        grun[d] = offsets[(size_t)d * gridDim.x + blockIdx.x];
+        if (!FEW) grun[d] = offsets[(size_t)d * gridDim.x + blockIdx.x];
         for (int i = 0; i < kSortWaves; ++i) wcnt[i][d] = 0;
     }
     __syncthreads();
@@ -441,23 +548,30 @@ __global__ __launch_bounds__(S::kBlock, S::kBlock == 256 ? 2 : 1) void radix_dow
     }
 }
 
+// Up to this many blocks a downsweep adds up the blocks' counts itself (each
+// reads all of them) instead of scanning them in three launches between the
+// sweeps: a pass takes 2 launches, not 5 (65,536
+// pairs in 16 blocks: about 55 -> 21 us a pass with the gaps; in 64 blocks of
+// 1024-key tiles, 14 us).
+constexpr unsigned kFewBlocks = 64;
+
 // One pass over digit [shift, shift + RB): histograms, their scan, the
 // stable scatter (values travel when vi is set).
-template <class K, int RB, class S>
+template <class K, int RB, class S, bool FEW>
 void sort_pass(const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, size_t n, int shift, unsigned nb, size_t tpb,
                uint64_t *hist, hipStream_t s)
 {
-    radix_upsweep<K, RB><<<nb, kSortBlock, 0, s>>>(ki, n, shift, tpb * S::kTile, hist);
+    radix_upsweep<K, RB, FEW><<<nb, kSortBlock, 0, s>>>(ki, n, shift, tpb * S::kTile, hist);
     TP_CHECK_LAUNCH();
-    scan_u64(hist, hist, (size_t)(1u << RB) * nb, false, s);
+    if (!FEW) scan_u64(hist, hist, (size_t)(1u << RB) * nb, false, s);
     if (vi)
-        radix_downsweep<K, true, RB, S><<<nb, S::kBlock, 0, s>>>(ki, vi, ko, vo, n, shift, tpb, hist);
+        radix_downsweep<K, true, RB, S, FEW><<<nb, S::kBlock, 0, s>>>(ki, vi, ko, vo, n, shift, tpb, hist);
     else
-        radix_downsweep<K, false, RB, S><<<nb, S::kBlock, 0, s>>>(ki, nullptr, ko, nullptr, n, shift, tpb, hist);
+        radix_downsweep<K, false, RB, S, FEW><<<nb, S::kBlock, 0, s>>>(ki, nullptr, ko, nullptr, n, shift, tpb, hist);
     TP_CHECK_LAUNCH();
 }
 
-template <class K, class S>
+template <class K, class S, bool FEW>
 bool radix_sort_shape(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, size_t n, int bits, hipStream_t s,
                       int begin_bit)
 {
@@ -476,8 +590,8 @@ bool radix_sort_shape(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, 
         const uint32_t *vi = in_alt ? vals_alt : vals;
         K *ko = in_alt ? keys : keys_alt;
         uint32_t *vo = in_alt ? vals : vals_alt;
-        if (pass < n10) sort_pass<K, 10, S>(ki, vi, ko, vo, n, shift, nb, tpb, hist.get(), s);
-        else sort_pass<K, 9, S>(ki, vi, ko, vo, n, shift, nb, tpb, hist.get(), s);
+        if (pass < n10) sort_pass<K, 10, S, FEW>(ki, vi, ko, vo, n, shift, nb, tpb, hist.get(), s);
+        else sort_pass<K, 9, S, FEW>(ki, vi, ko, vo, n, shift, nb, tpb, hist.get(), s);
         shift += pass < n10 ? 10 : 9;
         in_alt = !in_alt;
     }
@@ -499,8 +613,12 @@ bool radix_sort(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, size_t
                 int begin_bit)
 {
     if (n <= 1 || bits <= 0) return false;
-    if (sizeof(K) == 8 && n >= kWideKeys) return radix_sort_shape<K, SortWide>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
-    return radix_sort_shape<K, SortNarrow>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
+    if (sizeof(K) == 8 && n >= kWideKeys) return radix_sort_shape<K, SortWide, false>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
+    if (n <= (size_t)kFewBlocks * SortSmall::kTile)
+        return radix_sort_shape<K, SortSmall, true>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
+    if (n <= (size_t)kFewBlocks * SortNarrow::kTile)
+        return radix_sort_shape<K, SortNarrow, true>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
+    return radix_sort_shape<K, SortNarrow, false>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
 }
 
 }  // namespace

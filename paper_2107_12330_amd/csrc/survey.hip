@@ -2248,6 +2248,7 @@ extern "C" tp_status tripoll_max_edge_counts(const tp_graph *g, const tp_survey_
         if (g->n_graphs) fail(TP_ERR_UNSUPPORTED, "tripoll_max_edge_counts: single graphs only");
         if (g->m == 0 || g->n_in == 0) return;
         hipStream_t s = (hipStream_t)stream;
+        CallScope scope(s);
         // The largest time of a triangle is the time of one of its edges, so
         // each triangle is counted at that edge (the participation form of the
         // kernels: one of the three in LDS, one once per record, and only the
@@ -2527,6 +2528,7 @@ extern "C" tp_status tripoll_participation(const tp_graph *g, const tp_survey_sp
     return guard([&] {
         validate_spec(g, spec);
         hipStream_t s = (hipStream_t)stream;
+        CallScope scope(s);
         // the filters of the spec apply; its outputs do not.  A batch is
         // counted as the union of its graphs, which no triangle spans: its
         // vertex ids and CSR slots are those of the union, graph by graph
