@@ -103,6 +103,16 @@ constexpr uint32_t ring_size()
 // a drain leaves at most 127 queued; two sub-rows add at most 128 (the
 // doubled ring), one sub-row at most 64 (kRing)
 static_assert(2 * kRing >= (2 * kWave - 1) + 2 * kWave && kRing >= (kWave - 1) + kWave, "hit ring capacity");
+// Waves per SIMD a kernel's registers must leave room for: 8 in the per-wave
+// form of the plain survey (see survey_kernel) and in the count, as many as
+// their LDS lets reside for the 256-thread metadata survey.
+template <bool WAVE, int BLOCK, bool META, bool ENUM, int FORM>
+constexpr int min_waves()
+{
+    if (FORM != kFormSurvey || ENUM) return 1;
+    if (WAVE) return 8;
+    return BLOCK == 256 ? (META ? 5 : 8) : 1;
+}
 constexpr uint32_t kMaxKicks = 64;  // cuckoo displacements before a key goes to the stash
 
 // The two cuckoo hash functions, each onto 2^log_s slots: the low bits of
@@ -329,11 +339,22 @@ __device__ __forceinline__ bool passes_filters(const SurveyParams &P, const Hit 
     return true;
 }
 
+// A wave-uniform value read anew: its tests are then made where they are used.
+// (The compiler otherwise keeps the outcome of every test on the outputs in a
+// pair of scalar registers through the whole walk, where they are spilled.)
+__device__ __forceinline__ uint32_t fresh(uint32_t x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
 template <bool EXT, bool ARITH = false>
 __device__ __forceinline__ uint32_t reduce_hit(const SurveyParams &P, const Hit &h, unsigned long long *cnt,
                                                const uint64_t *mask_lds, const uint16_t *lut, uint32_t &spread)
 {
-    const uint32_t f = P.filters;
+    const uint32_t f = ARITH ? P.filters : fresh(P.filters), outs = ARITH ? P.outputs : fresh(P.outputs);
+    // (24-bit products issue at full rate)
+    auto copied = [&](uint32_t b) { return ARITH ? b * P.copies : (uint32_t)__umul24(b, P.copies); };
     if (f & TP_FILT_WINDOW) {
         if (P.window_empty) return 0;
         if (h.t_pq < P.t_lo32 || h.t_pq > P.t_hi32 || h.t_pr < P.t_lo32 || h.t_pr > P.t_hi32 ||
@@ -341,7 +362,7 @@ __device__ __forceinline__ uint32_t reduce_hit(const SurveyParams &P, const Hit 
             return 0;
     }
     uint32_t idx = 0;
-    if ((P.outputs & TP_OUT_LABEL_TABLE) || (f & TP_FILT_LABEL_MASK))
+    if ((outs & TP_OUT_LABEL_TABLE) || (f & TP_FILT_LABEL_MASK))
         idx = label_index<ARITH>(P, h, lut);
     if (f & TP_FILT_LABEL_MASK) {
         if (!((mask_lds[idx >> 6] >> (idx & 63)) & 1ull)) return 0;
@@ -351,21 +372,21 @@ __device__ __forceinline__ uint32_t reduce_hit(const SurveyParams &P, const Hit 
     const uint32_t close = t3 - t1;
     const CounterBase B = counter_base(P, EXT);
     const uint32_t cp = lane_id() & (P.copies - 1);
-    if (P.outputs & TP_OUT_CLOSE_HIST) atomicAdd(&cnt[close_bin(close) * P.copies + cp], 1ull);
-    if (P.outputs & TP_OUT_LABEL_TABLE) atomicAdd(&cnt[B.table + idx * P.copies + cp], 1ull);
-    if (P.outputs & TP_OUT_SPREAD_COUNT) spread += (P.spread_any && close <= P.spread_le) ? 1u : 0u;
-    if (P.outputs & TP_OUT_OPEN_CLOSE) {
+    if (outs & TP_OUT_CLOSE_HIST) atomicAdd(&cnt[copied(close_bin(close)) + cp], 1ull);
+    if (outs & TP_OUT_LABEL_TABLE) atomicAdd(&cnt[B.table + copied(idx) + cp], 1ull);
+    if (outs & TP_OUT_SPREAD_COUNT) spread += (P.spread_any && close <= P.spread_le) ? 1u : 0u;
+    if (outs & TP_OUT_OPEN_CLOSE) {
         const uint32_t t2 = h.t_pq + h.t_pr + h.t_qr - t1 - t3;  // exact in uint32 arithmetic mod 2^32
         atomicAdd(&cnt[B.oc + close_bin(t2 - t1) * 32 + close_bin(close)], 1ull);
     }
-    if (EXT && (P.outputs & TP_OUT_MAX_EDGE)) {
+    if (EXT && (outs & TP_OUT_MAX_EDGE)) {
         // Algorithm 3: vertex labels pairwise distinct; bin of the largest edge time
         if (h.l_p != h.l_q && h.l_q != h.l_r && h.l_p != h.l_r)
             atomicAdd(&cnt[B.maxe + min(t3 >> P.max_edge_shift, 1023u)], 1ull);
     }
-    if (EXT && (P.outputs & TP_OUT_DEGREE_TABLE))
+    if (EXT && (outs & TP_OUT_DEGREE_TABLE))
         atomicAdd(&cnt[B.deg + multiset_index(h.b_p, h.b_q, h.b_r)], 1ull);
-    if (EXT && (P.outputs & TP_OUT_DIRECTED))
+    if (EXT && (outs & TP_OUT_DIRECTED))
         atomicAdd(&cnt[B.dir + h.dtype], 1ull);
     return 1;
 }
@@ -459,6 +480,9 @@ __device__ __forceinline__ T sload(const T *p)
     __builtin_memcpy(&v, w, sizeof(T));
     return v;
 }
+
+typedef uint32_t uint32x3 __attribute__((ext_vector_type(3)));
+typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 
 // In-edge records as loaded: key (q << kbits) | k (or a piece's record) and
 // payload.  A block holds one in-edge per lane.
@@ -555,11 +579,12 @@ __device__ __forceinline__ uint64_t claim_tiles(const SurveyParams &P, ClaimBloc
 // per SIMD: its short tiles wait on chains of dependent loads, and more
 // waves hide them (20,000-graph batch survey 539.6 -> 515.3 ms).
 template <int LOG_SLOTS, int BLOCK, bool WAVE, bool META, bool ENUM, bool MULTI, int FORM, bool PIECES, bool WIDE>
-__global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 : 1) void survey_kernel(SurveyParams P)
+__global__ __launch_bounds__(BLOCK, (min_waves<WAVE, BLOCK, META, ENUM, FORM>())) void survey_kernel(SurveyParams P)
 {
     constexpr int kSub = Depth<WAVE>::kSub;
     constexpr int kBatch = Depth<WAVE>::kBatch;
     constexpr uint32_t kChunkCand = Depth<WAVE>::kChunkCand;
+    constexpr int kPair = kSub > 1 ? 2 : 1;     // sub-rows probed together
     constexpr int kWaves = BLOCK / kWave;       // waves per workgroup
     constexpr int kW = WAVE ? 1 : kWaves;       // waves sharing one table
     constexpr int kGroup = WAVE ? kWave : BLOCK;  // threads sharing one table
@@ -627,7 +652,17 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
     };
 
     const uint32_t lane = lane_id();
-    uint4 *ring = reinterpret_cast<uint4 *>(lds + L.off_ring) + (size_t)w * kRingK;
+    // a hit's fourth word (the pivot's degree bin and directions, or its id)
+    // is written by the extended and enumeration forms only (and by the
+    // per-wave form, whose 64 registers come out better so: 1200-graph batch's
+    // tiny class 9.0 against 10.6 ms)
+    using RingEntry = std::conditional_t<EXT || ENUM || WAVE, uint32x4, uint32x3>;
+    static_assert(sizeof(RingEntry) == 16, "ring entries are 16 bytes apart");
+    auto ring_w = [](const RingEntry &e) -> uint32_t {
+        if constexpr (EXT || ENUM || WAVE) return e.w;
+        else return 0u;
+    };
+    RingEntry *ring = reinterpret_cast<RingEntry *>(lds + L.off_ring) + (size_t)w * kRingK;
     for (uint32_t i = tid; i < nc * kGroups; i += BLOCK) cnt_all[i] = 0;
     if (tid < 13) mask_lds[tid] = P.label_mask[tid];
     if (tid < 3) s_tot[tid] = 0;
@@ -751,9 +786,9 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
     uint64_t pb_lo = 0, pb_hi = ~0ull;
     if (EXT && (P.outputs & TP_OUT_DEGREE_TABLE)) pb_hi = sload(P.dbin_slot + 1);
 
-    // reduce the hits queued in this wave's ring, one per lane; `gm` says
-    // where Adj+^m(q) is (true: HBM) at compile time, so that the table path
-    // holds no global load
+    // reduce the hits queued in this wave's ring, one per lane; `gm` says at
+    // compile time whether Adj+^m(q) may be in HBM (true: where gmode is set),
+    // so that the table path holds no global load
     auto drain = [&](uint32_t count, auto gm) {
         constexpr bool G = decltype(gm)::value;
         uint32_t tri = 0, spread = 0;
@@ -761,13 +796,14 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
         uint32_t e_p = 0, e_r = 0;  // original ids of p and r (enumeration)
         const bool valid = lane < count;
         if (valid) {
-            const uint4 e = ring[(qh + lane) & (kRingK - 1)];
+            const RingEntry e = ring[(qh + lane) & (kRingK - 1)];
+            const bool hbm = G && (LOG_SLOTS == 0 || gmode);
             const uint32_t where = e.x & 0x3fffffu;
             h.t_pq = e.z;
             h.l_p = e.x >> 22;
             h.l_q = l_q;
             h.t_pr = e.y;
-            if constexpr (!G) {
+            if (!hbm) {
                 h.t_qr = hts[where];
                 h.l_r = hlab[where];
             } else {
@@ -777,20 +813,20 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
             if (EXT && (P.outputs & TP_OUT_DEGREE_TABLE)) {
                 // the ring's last word holds the pivot's degree bin; the
                 // table keeps that of every key
-                h.b_p = e.w & 0xffu;
+                h.b_p = ring_w(e) & 0xffu;
                 h.b_q = bin_q;
-                h.b_r = !G ? hbin[where] : degree_bin_of(dbin_g, P.col[kq + where]);
+                h.b_r = !hbm ? hbin[where] : degree_bin_of(dbin_g, P.col[kq + where]);
             }
             if (kdir) {
                 // ... and the directions of (p, q) and (p, r) above it
-                const uint32_t dqr = !G ? hdir[where] : P.edir[kq + where];
-                h.dtype = dtype_lds[(((e.w >> 8) & 3u) << 4) | (((e.w >> 10) & 3u) << 2) | (dqr & 3u)];
+                const uint32_t dqr = !hbm ? hdir[where] : P.edir[kq + where];
+                h.dtype = dtype_lds[(((ring_w(e) >> 8) & 3u) << 4) | (((ring_w(e) >> 10) & 3u) << 2) | (dqr & 3u)];
             }
             if (ENUM) {
                 // original ids: of r from the table (or through the CSR in
                 // HBM), of p from the ring
-                e_r = !G ? hpos[where] : P.perm[P.col[kq + where]];
-                e_p = e.w;
+                e_r = !hbm ? hpos[where] : P.perm[P.col[kq + where]];
+                e_p = ring_w(e);
             } else if (!MULTI) {
                 tri = reduce_hit<EXT, WAVE>(P, h, cnt, mask_lds, lut, spread);
             }
@@ -843,12 +879,13 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
     auto drain2 = [&](auto gm) {
         constexpr bool G = decltype(gm)::value;
         __builtin_amdgcn_s_setprio(2);
-        const uint4 e0 = ring[(qh + lane) & (kRingK - 1)];
-        const uint4 e1 = ring[(qh + kWave + lane) & (kRingK - 1)];
+        const RingEntry e0 = ring[(qh + lane) & (kRingK - 1)];
+        const RingEntry e1 = ring[(qh + kWave + lane) & (kRingK - 1)];
+        const bool hbm = G && (LOG_SLOTS == 0 || gmode);
         const uint32_t w0 = e0.x & 0x3fffffu, w1 = e1.x & 0x3fffffu;
         Hit h0{e0.z, e0.y, 0, e0.x >> 22, l_q, 0, 0, 0, 0, 0};
         Hit h1{e1.z, e1.y, 0, e1.x >> 22, l_q, 0, 0, 0, 0, 0};
-        if constexpr (!G) {
+        if (!hbm) {
             h0.t_qr = hts[w0];
             h1.t_qr = hts[w1];
             h0.l_r = hlab[w0];
@@ -867,17 +904,17 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
         qh = __builtin_amdgcn_readfirstlane(qh + 2 * kWave);
         __builtin_amdgcn_s_setprio(0);
     };
+    auto put_hit = [&](uint32_t at, uint32_t x, uint32_t y, uint32_t z, uint32_t w4) {
+        if constexpr (EXT || ENUM || WAVE) ring[at & (kRingK - 1)] = RingEntry{x, y, z, w4};
+        else ring[at & (kRingK - 1)] = RingEntry{x, y, z};
+    };
     auto drain_queued = [&]() {
         if constexpr (kRingK > kRing) {
             // the doubled ring may hold more than a wave's 64
-            while (qt - qh > (uint32_t)kWave) {
-                if (gmode) drain(kWave, std::true_type{});
-                else drain(kWave, std::false_type{});
-            }
+            while (qt - qh > (uint32_t)kWave) drain(kWave, std::true_type{});
         }
         if (qt == qh) return;
-        if (gmode) drain(qt - qh, std::true_type{});
-        else drain(qt - qh, std::false_type{});
+        drain(qt - qh, std::true_type{});
     };
     // participation: add the table's per-slot counts of edges (q, r) into
     // their CSR slots; every thread of the group calls it once the group is
@@ -915,7 +952,12 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
         } else {
             if (tid == 0) s_tile = atomicAdd(P.tile_counter + seg, 1ull);
             __syncthreads();
-            t_begin = seg_lo + s_tile * kClaim;
+            // (in scalar registers: with a claim that the compiler takes for
+            // one per lane, the loops below and all that they update would be
+            // kept per lane too)
+            const unsigned long long c = s_tile;
+            t_begin = seg_lo + (((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(c >> 32)) << 32) |
+                                (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)c)) * kClaim;
             __syncthreads();  // everyone has read s_tile before it is claimed again
             if (t_begin >= seg_hi) {
                 // the segment is used up (its counter only grows): the next one
@@ -1052,6 +1094,15 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                     }
                 }
                 gsync();
+            }
+
+            // the same in every lane, which the compiler cannot tell past the
+            // table's loops: in scalar registers, or the whole walk (its
+            // branches, cursors and counts) would be kept per lane
+            // (not in the per-wave form, which has no scalar registers to spare)
+            if (!WAVE) {
+                gmode = __builtin_amdgcn_readfirstlane((int)gmode) != 0;
+                n_stash = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_stash);
             }
 
             // ---- this wave's records: tile records w, w + kW, w + 2kW, ...,
@@ -1211,7 +1262,7 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                             if ((m >> lane) & 1ull) {
                                 const uint32_t below = __builtin_amdgcn_mbcnt_hi(
                                     (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                                ring[(qt + below) & (kRingK - 1)] = make_uint4(slot | (st.lp << 22), st.tpr, st.tpq, 0u);
+                                put_hit(qt + below, slot | (st.lp << 22), st.tpr, st.tpq, 0u);
                             }
                             qt = __builtin_amdgcn_readfirstlane(qt + (uint32_t)__popcll(m));
                             if (qt - qh >= (uint32_t)kWave) drain(kWave, gm);
@@ -1294,6 +1345,7 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                 WaveRec rec = read_rec(0);
                 uint32_t off = 0; // next slot of the current record
                 uint32_t wave_work = 0, wave_hits = 0;
+                uint32_t lane_hits = 0;  // count only: this lane's
                 // participation: the record whose (p, q) the wave is counting
                 uint64_t pq_slot = 0;
                 uint32_t pq_hits = 0;
@@ -1380,47 +1432,66 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
     #pragma unroll
                     for (int c = 0; c < kBatch; ++c) {
     #pragma unroll
-                        for (int sr = 0; sr < kSub; ++sr) {
+                        for (int s2 = 0; s2 < kSub; s2 += kPair) {
                             if constexpr (kRingK > kRing) {
                                 // the doubled ring takes two sub-rows of hits (at most
                                 // 128) above 127 queued: drained before every other
                                 // sub-row only, so that the unrolled walk holds half
                                 // the copies of the reduction (large class 316.5 ->
                                 // 311.5 ms)
-                                if ((sr & 1) == 0 && qt - qh >= 2u * kWave) drain2(gm);
+                                if (qt - qh >= 2u * kWave) drain2(gm);
                             }
-                            if (chs[c].n <= (uint32_t)(sr * kWave)) break;
-                            const uint32_t nsub = min(chs[c].n - sr * kWave, (uint32_t)kWave);
-                            // lanes >= nsub hold no candidate (they read 0): mask their hits
-                            const uint64_t live = nsub >= (uint32_t)kWave ? ~0ull : ((1ull << nsub) - 1);
+                            if (chs[c].n <= (uint32_t)(s2 * kWave)) break;
+                            // Lanes past the chunk's end hold candidate 0, which is in
+                            // no out-list (its targets have higher ranks than their
+                            // sources) and so in no table: their hits need no mask.
+                            // The table reads of two sub-rows are issued together.
+                            const bool two = kPair > 1 && chs[c].n > (uint32_t)((s2 + 1) * kWave);
+                            bool hit[kPair];
+                            uint32_t slot[kPair];
+                            uint32_t a0[kPair], a1[kPair], k0[kPair], k1[kPair];
+                            if (!G || (LOG_SLOTS > 0 && !gmode)) {
+    #pragma unroll
+                                for (int x = 0; x < kPair; ++x) {
+                                    if (x && !two) break;
+                                    const uint32_t v = cand[c][s2 + x];
+                                    a0[x] = hash0(v, log_s);
+                                    a1[x] = (1u << log_s) + hash1(v, log_s);
+                                    k0[x] = hkey[a0[x]];
+                                    k1[x] = hkey[a1[x]];
+                                }
+                            }
+    #pragma unroll
+                          for (int x = 0; x < kPair; ++x) {
+                            if (x && !two) break;
+                            const int sr = s2 + x;
                             const uint32_t r = cand[c][sr];
-                            bool hit;
-                            uint32_t slot;
-                            if constexpr (!G) {
-                                // two independent reads, no loop
-                                const uint32_t h0 = hash0(r, log_s), h1 = (1u << log_s) + hash1(r, log_s);
-                                const uint32_t k0 = hkey[h0], k1 = hkey[h1];
-                                hit = k0 == r || k1 == r;
-                                slot = k0 == r ? h0 : h1;
-                                if (n_stash) {
+                            if (!G || (LOG_SLOTS > 0 && !gmode)) {
+                                hit[x] = k0[x] == r || k1[x] == r;
+                                slot[x] = k0[x] == r ? a0[x] : a1[x];
+                                if (G) {
                                     const uint32_t st = 2u << log_s;
-                                    for (uint32_t x = 0; x < n_stash; ++x) {
-                                        if (hkey[st + x] == r) {
-                                            hit = true;
-                                            slot = st + x;
+                                    for (uint32_t y = 0; y < n_stash; ++y) {
+                                        if (hkey[st + y] == r) {
+                                            hit[x] = true;
+                                            slot[x] = st + y;
                                         }
                                     }
                                 }
                             } else {
-                                hit = false;
-                                slot = 0;
-                                if (lane < nsub) {
+                                hit[x] = false;
+                                slot[x] = 0;
+                                if (lane + (uint32_t)(sr * kWave) < chs[c].n) {
                                     const int64_t at = global_find(P.col, kq, dq, r);
-                                    hit = at >= 0;
-                                    slot = (uint32_t)(at - (int64_t)kq);
+                                    hit[x] = at >= 0;
+                                    slot[x] = (uint32_t)(at - (int64_t)kq);
                                 }
                             }
-                            const uint64_t m = __ballot(hit) & live;
+                            if (!META && !ENUM) {
+                                lane_hits += hit[x] ? 1u : 0u;
+                                continue;
+                            }
+                            const uint64_t m = __ballot(hit[x]);
                             if constexpr (PART) {
                                 // local participation: one count for each edge of
                                 // every triangle that passes the prefilters
@@ -1428,20 +1499,20 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                                 uint32_t at = kAtAll;
                                 if (pass && (P.filters || P.part_top)) {
                                     Hit h{chs[c].t_pq, tpr[c][sr], 0, chs[c].l_p, l_q, 0, 0, 0, 0};
-                                    if constexpr (!G) {
-                                        h.t_qr = hts[slot];
-                                        h.l_r = hlab[slot];
+                                    if (!G || (LOG_SLOTS > 0 && !gmode)) {
+                                        h.t_qr = hts[slot[x]];
+                                        h.l_r = hlab[slot[x]];
                                     } else {
-                                        h.t_qr = P.ets[kq + slot];
-                                        h.l_r = P.tlab[kq + slot];
+                                        h.t_qr = P.ets[kq + slot[x]];
+                                        h.l_r = P.tlab[kq + slot[x]];
                                     }
                                     pass = part_passes<WAVE>(P, h, mask_lds, lut, at);
                                 }
                                 if (pass && (at == kAtAll || at == kAtPR))
                                     atomicAdd(&P.part_edge[chs[c].base + (uint32_t)(sr * kWave) + lane], 1u);  // (p, r)
                                 if (pass && (at == kAtAll || at == kAtQR)) {
-                                    if constexpr (!G) atomicAdd(&hcnt[slot], 1u);  // (q, r), per table slot
-                                    else atomicAdd(&P.part_edge[kq + slot], 1u);
+                                    if (!G || (LOG_SLOTS > 0 && !gmode)) atomicAdd(&hcnt[slot[x]], 1u);  // (q, r), per table slot
+                                    else atomicAdd(&P.part_edge[kq + slot[x]], 1u);
                                 }
                                 // (p, q): one add per record, when the next one's first sub-row comes
                                 if (chs[c].spq != pq_slot) {
@@ -1452,18 +1523,13 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                                 wave_hits += (uint32_t)__popcll(__ballot(pass));
                                 continue;
                             }
-                            if (!META && !ENUM) {
-                                wave_hits += (uint32_t)__popcll(m);
-                                continue;
-                            }
                             if (m) {
                                 if ((m >> lane) & 1ull) {
                                     // position among the wave's hits: hits in the lanes below
                                     const uint32_t below = __builtin_amdgcn_mbcnt_hi(
                                         (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                                    ring[(qt + below) & (kRingK - 1)] =
-                                        make_uint4(slot | (chs[c].l_p << 22), tpr[c][sr], chs[c].t_pq,
-                                                   EXT && kdir ? chs[c].p | ((dpr[c][sr] & 3u) << 10) : chs[c].p);
+                                    put_hit(qt + below, slot[x] | (chs[c].l_p << 22), tpr[c][sr], chs[c].t_pq,
+                                            EXT && kdir ? chs[c].p | ((dpr[c][sr] & 3u) << 10) : chs[c].p);
                                 }
                                 // the ring cursors are wave-uniform: keep them in scalar registers
                                 qt = __builtin_amdgcn_readfirstlane(qt + (uint32_t)__popcll(m));
@@ -1471,6 +1537,7 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                                     if (qt - qh >= (uint32_t)kWave) drain(kWave, gm);
                                 }
                             }
+                          }
                         }
                     }
                 };
@@ -1489,13 +1556,21 @@ __global__ __launch_bounds__(BLOCK, (WAVE && FORM == kFormSurvey && !ENUM) ? 8 :
                     if (rA[0].n == 0) break;
                 }
                 flush_pq();
+                my_tri += lane_hits;
                 if (lane == 0) {
                     probes += wave_work;
                     my_tri += wave_hits;
                 }
             };
-            if (gmode) walk(std::true_type{});
-            else walk(std::false_type{});
+            // (the per-wave tables' walk takes their stash along: it serves all
+            // but the HBM search; the others leave a table with a stash, which
+            // few targets have, to the general walk)
+            if constexpr (LOG_SLOTS == 0) {
+                walk(std::true_type{});
+            } else {
+                if (gmode || (!kGroupWalk && n_stash)) walk(std::true_type{});
+                else walk(std::false_type{});
+            }
             // a streamed or counted enumeration places records by tile: the
             // ring must not carry them into the next tile
             if (ENUM && (P.enum_tile_base || P.enum_tile_count)) drain_queued();
