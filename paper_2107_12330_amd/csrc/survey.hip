@@ -43,6 +43,11 @@ namespace {
 
 constexpr int kSmallBlock = 256;   // 4 waves share a small target's tables
 constexpr int kLargeBlock = 1024;  // 16 waves share a large target's tables
+// The forms whose counters or tables are larger let 8 waves share a small
+// target's: more waves fit the compute unit's LDS (extended survey, scale 21:
+// 20.6 -> 14.0 ms; exact counting set 8.2 -> 7.5 ms; eight served requests 14.0
+// -> 11.5 ms; participation, scale 22: 18.4 -> 18.1 ms).
+constexpr int kSmallBlockWide = 512;
 // Candidate loads in flight per wave: a chunk is kSub sub-rows of 64
 // candidates of one record, a batch is kBatch chunks, and two batches are in
 // flight.  The per-wave form serves short rows (tiny targets, small graphs;
@@ -100,6 +105,11 @@ constexpr uint32_t ring_size()
 {
     return (WIDE && !WAVE && BLOCK == 1024 && META && !ENUM && !MULTI && FORM == kFormSurvey) ? 2 * kRing : kRing;
 }
+template <bool MULTI, int FORM>
+constexpr int small_block()
+{
+    return MULTI || FORM != kFormSurvey ? kSmallBlockWide : kSmallBlock;
+}
 // a drain leaves at most 127 queued; two sub-rows add at most 128 (the
 // doubled ring), one sub-row at most 64 (kRing)
 static_assert(2 * kRing >= (2 * kWave - 1) + 2 * kWave && kRing >= (kWave - 1) + kWave, "hit ring capacity");
@@ -109,6 +119,7 @@ static_assert(2 * kRing >= (2 * kWave - 1) + 2 * kWave && kRing >= (kWave - 1) +
 template <bool WAVE, int BLOCK, bool META, bool ENUM, int FORM>
 constexpr int min_waves()
 {
+    if (BLOCK == kSmallBlockWide) return FORM == kFormExt ? 4 : 6;
     if (FORM != kFormSurvey || ENUM) return 1;
     if (WAVE) return 8;
     return BLOCK == 256 ? (META ? 5 : 8) : 1;
@@ -1742,6 +1753,7 @@ uint32_t table_size(uint32_t L) { return (L + 2) * (L + 1) * L / 6; }
 // Dynamic LDS a workgroup may take: 160 KiB per compute unit, less room for
 // the kernel's static arrays.
 constexpr size_t kLdsLimit = 160 * 1024 - 4096;
+constexpr size_t kLdsStatic = 512;  // more than the plain survey's static arrays
 
 template <int LOG_SLOTS, int BLOCK, bool WAVE, bool META, bool ENUM, bool MULTI, int FORM, bool WIDE = false>
 size_t lds_need(const SurveyParams &P)
@@ -1864,11 +1876,22 @@ void launch_variant(int c, uint32_t v, const SurveyParams &P0, hipStream_t s, in
             if (lds_need<kLargeLogSlots, kLargeBlock, false, META, ENUM, MULTI, FORM, true>(P) <= kLdsLimit)
                 top = kMaxCopiesLarge;
         }
+        if (META && !ENUM && !MULTI && FORM == kFormSurvey && log_slots == kSmallLogSlots) {
+            // fewer copies where they let another workgroup reside (five at
+            // most, by their registers): 8 labels' table in 2 copies instead
+            // of 4 (scale 22: 11.8 -> 11.1 ms)
+            auto fit = [&](uint32_t k) {
+                P.copies = k;
+                const size_t need = lds_need<kSmallLogSlots, kSmallBlock, false, META, ENUM, MULTI, FORM>(P) + kLdsStatic;
+                return std::min<size_t>(5, 160 * 1024 / need);
+            };
+            while (top > 1 && fit(top / 2) > fit(top)) top /= 2;
+        }
         for (P.copies = top; P.copies > 1; P.copies /= 2) {
             size_t need = 0;
             if (log_slots == kTinyLogSlots && wave) need = lds_need<kTinyLogSlots, kSmallBlock, true, META, ENUM, MULTI, FORM>(P);
             else if (log_slots == kLargeLogSlots) need = lds_need<kLargeLogSlots, kLargeBlock, false, META, ENUM, MULTI, FORM>(P);
-            else if (log_slots == kSmallLogSlots) need = lds_need<kSmallLogSlots, kSmallBlock, false, META, ENUM, MULTI, FORM>(P);
+            else if (log_slots == kSmallLogSlots) need = lds_need<kSmallLogSlots, small_block<MULTI, FORM>(), false, META, ENUM, MULTI, FORM>(P);
             else if (wave) need = lds_need<0, kSmallBlock, true, META, ENUM, MULTI, FORM>(P);
             else need = lds_need<0, kSmallBlock, false, META, ENUM, MULTI, FORM>(P);
             if (need <= kLdsLimit) break;
@@ -1901,8 +1924,8 @@ void launch_variant(int c, uint32_t v, const SurveyParams &P0, hipStream_t s, in
     case TP_VAR_GROUP_TABLE:
         if (c == kClassLarge && lds_need<kLargeLogSlots, kLargeBlock, false, META, ENUM, MULTI, FORM>(P) <= kLdsLimit)
             launch_class<kLargeLogSlots, kLargeBlock, false, META, ENUM, MULTI, FORM>(P, s, device);
-        else if (c != kClassLarge && lds_need<kSmallLogSlots, kSmallBlock, false, META, ENUM, MULTI, FORM>(P) <= kLdsLimit)
-            launch_class<kSmallLogSlots, kSmallBlock, false, META, ENUM, MULTI, FORM>(P, s, device);
+        else if (c != kClassLarge && lds_need<kSmallLogSlots, small_block<MULTI, FORM>(), false, META, ENUM, MULTI, FORM>(P) <= kLdsLimit)
+            launch_class<kSmallLogSlots, small_block<MULTI, FORM>(), false, META, ENUM, MULTI, FORM>(P, s, device);
         else
             launch_class<0, kSmallBlock, false, META, ENUM, MULTI, FORM>(P, s, device);
         break;
