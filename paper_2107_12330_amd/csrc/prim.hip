@@ -323,8 +323,8 @@ void scan_u32_to_u64(const uint32_t *in, uint64_t *out, size_t n, hipStream_t s)
 // A fixed number of blocks each own a contiguous chunk of tiles (4096
 // keys).  Per pass:
 //   1. upsweep: digit histogram of each block's chunk -> hist[digit][block]
-//   2. exclusive scan of hist (digit-major), giving each (digit, block) its
-//      first output position
+//   2. exclusive scan of each digit's row of hist, and the rows' totals, from
+//      which each (digit, block) has its first output position
 //   3. downsweep: per tile, each wave ranks its quarter of the tile stably
 //      with ballot-based digit matching; the tile is reordered in LDS by
 //      digit and written out in digit runs, so stores are contiguous.
@@ -432,11 +432,31 @@ __global__ __launch_bounds__(S::kBlock, S::kRounds == 16 ? 2 : 1) void radix_dow
                 at += all[j];
             }
         }
+    } else {
+        // all smaller digits (their totals follow the rows), then this digit
+        // in the blocks before (the scanned row)
+        const uint64_t *total = offsets + (size_t)kRadix * gridDim.x;
+        uint64_t sum = 0, all[kDigitsPerThread];
+        const bool mine = kDigitThreads == kSortBlock || (int)threadIdx.x < kDigitThreads;
+#pragma unroll
+        for (int j = 0; j < kDigitsPerThread; ++j) {
+            all[j] = mine ? total[threadIdx.x * kDigitsPerThread + j] : 0ull;
+            sum += all[j];
+        }
+        __shared__ uint64_t wide_tmp[kSortWaves];
+        uint64_t end;
+        uint64_t at = block_excl_scan<kSortBlock>(sum, wide_tmp, end);
+        if (mine) {
+#pragma unroll
+            for (int j = 0; j < kDigitsPerThread; ++j) {
+                const unsigned d = threadIdx.x * kDigitsPerThread + j;
+                grun[d] = at + offsets[(size_t)d * gridDim.x + blockIdx.x];
+                at += all[j];
+            }
+        }
     }
-    for (int d = threadIdx.x; d < kRadix; d += kSortBlock) {
-        if (!FEW) grun[d] = offsets[(size_t)d * gridDim.x + blockIdx.x];
+    for (int d = threadIdx.x; d < kRadix; d += kSortBlock)
         for (int i = 0; i < kSortWaves; ++i) wcnt[i][d] = 0;
-    }
     __syncthreads();
 
     const size_t t0 = blockIdx.x * tiles_per_block;
@@ -548,9 +568,35 @@ __global__ __launch_bounds__(S::kBlock, S::kRounds == 16 ? 2 : 1) void radix_dow
     }
 }
 
+// One block per digit: the exclusive scan of its row of block counts, in
+// place, and the row's total past the rows.  Each downsweep block scans the
+// totals over the digits itself, so that a pass takes three launches where a
+// scan of the whole table took five (300,007 vertices, 3.3e6 raw edges, 14
+// passes: build and survey 2.32 -> 2.11 ms).
+static_assert(kMaxSortBlocks <= kSortBlock * 8, "a row is scanned by one block of 8 counts a thread");
+__global__ __launch_bounds__(kSortBlock) void radix_rows(uint64_t *hist, unsigned blocks)
+{
+    __shared__ uint64_t tmp[kSortBlock / kWave];
+    uint64_t *row = hist + (size_t)blockIdx.x * blocks;
+    uint64_t v[8], sum = 0;
+    const unsigned b0 = threadIdx.x * 8;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        v[j] = b0 + j < blocks ? row[b0 + j] : 0ull;
+        sum += v[j];
+    }
+    uint64_t total;
+    uint64_t at = block_excl_scan<kSortBlock>(sum, tmp, total);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (b0 + j < blocks) row[b0 + j] = at;
+        at += v[j];
+    }
+    if (threadIdx.x == 0) hist[(size_t)gridDim.x * blocks + blockIdx.x] = total;
+}
+
 // Up to this many blocks a downsweep adds up the blocks' counts itself (each
-// reads all of them) instead of scanning them in three launches between the
-// sweeps: a pass takes 2 launches, not 5 (65,536
+// reads all of them): a pass takes 2 launches (65,536
 // pairs in 16 blocks: about 55 -> 21 us a pass with the gaps; in 64 blocks of
 // 1024-key tiles, 14 us).
 constexpr unsigned kFewBlocks = 64;
@@ -563,7 +609,10 @@ void sort_pass(const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, size_t n, i
 {
     radix_upsweep<K, RB, FEW><<<nb, kSortBlock, 0, s>>>(ki, n, shift, tpb * S::kTile, hist);
     TP_CHECK_LAUNCH();
-    if (!FEW) scan_u64(hist, hist, (size_t)(1u << RB) * nb, false, s);
+    if (!FEW) {
+        radix_rows<<<1u << RB, kSortBlock, 0, s>>>(hist, nb);
+        TP_CHECK_LAUNCH();
+    }
     if (vi)
         radix_downsweep<K, true, RB, S, FEW><<<nb, S::kBlock, 0, s>>>(ki, vi, ko, vo, n, shift, tpb, hist);
     else
@@ -578,7 +627,7 @@ bool radix_sort_shape(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, 
     const size_t tiles = (n + S::kTile - 1) / S::kTile;
     const unsigned nb = (unsigned)std::min<size_t>(tiles, kMaxSortBlocks);
     const size_t tpb = (tiles + nb - 1) / nb;
-    DArray<uint64_t> hist((size_t)(1u << kMaxRadixBits) * nb, s);
+    DArray<uint64_t> hist((size_t)(1u << kMaxRadixBits) * (nb + 1), s);  // the rows, then their totals
     // 9-bit digits, or as few 10-bit ones as cover `bits` in one pass less
     const int p9 = (bits + 8) / 9, p10 = (bits + 9) / 10;
     const int passes = std::min(p9, p10);
@@ -633,6 +682,51 @@ bool radix_sort_pairs32(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint
                         hipStream_t s)
 {
     return radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, s, 0);
+}
+
+// Partition by the top bits: one pass of the sort.  The blocks' scanned rows
+// hold each digit's place only relative to the digit, so the starts are summed
+// from the totals here.
+namespace {
+template <int RB>
+__global__ __launch_bounds__(kSortBlock) void partition_starts(const uint64_t *total, uint64_t n, uint64_t *start)
+{
+    __shared__ uint64_t tmp[kSortBlock / kWave];
+    constexpr int kPer = (1 << RB) / kSortBlock;
+    uint64_t v[kPer], sum = 0, all;
+    for (int j = 0; j < kPer; ++j) {
+        v[j] = total[threadIdx.x * kPer + j];
+        sum += v[j];
+    }
+    uint64_t at = block_excl_scan<kSortBlock>(sum, tmp, all);
+    for (int j = 0; j < kPer; ++j) {
+        start[threadIdx.x * kPer + j] = at;
+        at += v[j];
+    }
+    if (threadIdx.x == 0) start[1 << RB] = n;
+}
+
+template <int RB>
+void partition(const uint32_t *keys, uint32_t *out, size_t n, int shift, uint64_t *start, hipStream_t s)
+{
+    using S = SortNarrow;
+    const size_t tiles = (n + S::kTile - 1) / S::kTile;
+    const unsigned nb = (unsigned)std::min<size_t>(tiles, kMaxSortBlocks);
+    const size_t tpb = (tiles + nb - 1) / nb;
+    DArray<uint64_t> hist((size_t)(1u << RB) * (nb + 1), s);
+    sort_pass<uint32_t, RB, S, false>(keys, nullptr, out, nullptr, n, shift, nb, tpb, hist.get(), s);
+    partition_starts<RB><<<1, kSortBlock, 0, s>>>(hist.get() + (size_t)(1u << RB) * nb, n, start);
+    TP_CHECK_LAUNCH();
+}
+}  // namespace
+
+int partition_bits(int bits) { return bits <= 24 ? 9 : 10; }
+
+void partition_u32(const uint32_t *keys, uint32_t *out, size_t n, int bits, uint64_t *start, hipStream_t s)
+{
+    const int rb = partition_bits(bits);
+    if (rb == 9) partition<9>(keys, out, n, bits - rb, start, s);
+    else partition<10>(keys, out, n, bits - rb, start, s);
 }
 
 bool radix_sort_u32(uint32_t *keys, uint32_t *keys_alt, size_t n, int bits, hipStream_t s, int begin_bit)

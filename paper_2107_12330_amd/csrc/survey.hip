@@ -2378,7 +2378,7 @@ extern "C" tp_status tripoll_max_edge_counts(const tp_graph *g, const tp_survey_
         TP_CHECK_LAUNCH();
         unsigned long long *mx = res.get();  // (the survey's words are done with)
         zero_u64<<<1, 64, 0, s>>>(mx, 1);
-        k_max_u32<<<grid_for(k, 256, kStatBlocks), 256, 0, s>>>(va.get(), k, mx);
+        k_max_u32<<<stat_grid(k, 256), 256, 0, s>>>(va.get(), k, mx);
         TP_CHECK_LAUNCH();
         unsigned long long top = 0;
         TP_HIP(hipMemcpyAsync(&top, mx, 8, hipMemcpyDeviceToHost, s));
@@ -2553,7 +2553,7 @@ extern "C" tp_status tripoll_enum_open(const tp_graph *g, const tp_survey_spec *
         zero_u64<<<1, 64, 0, s>>>(mx, 1);
         TP_CHECK_LAUNCH();
         if (T) {
-            k_max_u32<<<grid_for(T, 256, kStatBlocks), 256, 0, s>>>(count.get(), T, mx);
+            k_max_u32<<<stat_grid(T, 256), 256, 0, s>>>(count.get(), T, mx);
             TP_CHECK_LAUNCH();
         }
         uint64_t h[2] = {0, 0};

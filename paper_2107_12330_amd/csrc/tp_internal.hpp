@@ -259,9 +259,14 @@ __device__ __forceinline__ void block_max(unsigned long long v, unsigned long lo
     __syncthreads();
 }
 
-// Blocks of a pass that ends in such an atomic: enough to fill the device
-// (8 a compute unit), few enough that the atomics take some 20 us.
-constexpr unsigned kStatBlocks = 2048;
+// Blocks of a pass over n elements that ends in such an atomic: at most enough
+// to fill the device (8 a compute unit), whose atomics take some 20 us, and 8
+// elements a thread where there are fewer.
+inline unsigned stat_grid(size_t n, int block)
+{
+    const size_t g = (n + (size_t)block * 8 - 1) / ((size_t)block * 8);
+    return (unsigned)(g < 1 ? 1 : (g > 2048 ? 2048 : g));
+}
 
 // ---------------------------------------------------------------- primitives (prim.hip)
 
@@ -276,7 +281,12 @@ void scan_u32_to_u64(const uint32_t *in, uint64_t *out, size_t n, hipStream_t s)
 // the same size.  Returns true when the result ended in the alt buffers.
 bool radix_sort_pairs(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *vals_alt, size_t n,
                       int bits, hipStream_t s, int begin_bit = 0);
-// The same for 32-bit keys with values, and for 32-bit keys alone.
+// Partition of n > 0 keys of `bits` bits (at least 10) by their top
+// partition_bits(bits) bits, in one pass; start[d] is the first key of digit
+// d's (start holds 2^partition_bits + 1).
+int partition_bits(int bits);
+void partition_u32(const uint32_t *keys, uint32_t *out, size_t n, int bits, uint64_t *start, hipStream_t s);
+// Radix sorts of 32-bit keys with values, and of 32-bit keys alone.
 bool radix_sort_pairs32(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt, size_t n, int bits,
                         hipStream_t s);
 bool radix_sort_u32(uint32_t *keys, uint32_t *keys_alt, size_t n, int bits, hipStream_t s, int begin_bit = 0);

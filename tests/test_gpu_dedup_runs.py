@@ -129,3 +129,26 @@ def test_survey_after_many_builds(T):
             assert got["triangles"] == r["triangles"] and np.array_equal(got["close_hist"], r["close_hist"])
     for H, _ in held:
         H.close()
+
+
+@pytest.mark.parametrize("n", [4097, 8191, 8192, 8193, 1 << 17, (1 << 19) + 3])
+@pytest.mark.parametrize("hub", [False, True])
+def test_degrees_counted_by_parts(T, n, hub):
+    """Degrees counted from a partition of the higher ends (from 2^20 edges of
+    at least 13-bit ids on): every degree, through the order it gives, with
+    the ends spread evenly or mostly at one vertex's part."""
+    print("vertices", n, "hub", hub, flush=True)
+    rng = np.random.default_rng(n)
+    m = 2400000
+    src, dst = (rng.integers(0, n, m).astype(np.uint32) for _ in range(2))
+    if hub:
+        dst[: m // 2] = n - 1 - rng.integers(0, min(n, 700), m // 2).astype(np.uint32)
+    G, keep = build(T, n, src, dst, np.zeros(m, np.uint32))
+    with G:
+        st, x = G.stats(), tp.export(G)
+    lo, hi = np.minimum(src, dst).astype(np.int64), np.maximum(src, dst).astype(np.int64)
+    uk = np.unique((lo * n + hi)[lo != hi])
+    assert len(uk) >= 1 << 20 and st["n_edges"] == len(uk)
+    deg = np.bincount(uk // n, minlength=n) + np.bincount(uk % n, minlength=n)
+    assert st["d_max"] == deg.max()
+    assert np.array_equal(x["rank_to_id"], np.lexsort((np.arange(n), deg)))
