@@ -649,9 +649,12 @@ bool radix_sort_shape(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, 
 
 // All passes of a sort of at most kOneKeys pairs in one workgroup: keys and
 // values stay in registers (wave w's in places [64 r w, 64 r (w + 1)), r rounds)
-// and trade places through LDS.  One launch, where the smallest shape takes two
-// a pass (4096 vertices' order keys, 24 bits: 30 us less with the launches' gaps, 728 to
-// 698 us of a build and survey of 2^16 edges).
+// and trade places through LDS.  What bounds sorts of this size is the launches
+// and a pass's chain of waits: here one launch, 17 us for 4096 keys of 24 bits,
+// where the smallest shape takes two launches a pass.  A build of 1000 / 8000
+// edges (both its sorts): 395 -> 307 / 451 -> 392 us; of 2^16 edges with 4096
+// vertices (the order only), with its survey: 728 -> 698; at 8192 vertices and
+// 30,000 edges still 498 -> 453.
 constexpr int kOneBlock = 1024;
 constexpr int kOneRounds = 8;
 constexpr size_t kOneKeys = (size_t)kOneBlock * kOneRounds;
