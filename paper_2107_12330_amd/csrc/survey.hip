@@ -2352,7 +2352,7 @@ extern "C" tp_status tripoll_max_edge_counts(const tp_graph *g, const tp_survey_
         // kernels: one of the three in LDS, one once per record, and only the
         // third with a device atomic), and the edges' counts are then summed
         // by time.  A hash table of the times, with two random device atomics
-        // per triangle, took 27.6 ms on the scale-21 graph, this takes 10.5 ms.
+        // per triangle, took the call 32.0 ms on the scale-21 graph, this 8.9 ms.
         DArray<unsigned long long> res(TP_RESULT_WORDS, s);
         DArray<uint32_t> edge(g->m, s);
         fill<uint32_t>(edge.get(), 0u, g->m, s);
