@@ -320,7 +320,7 @@ void scan_u32_to_u64(const uint32_t *in, uint64_t *out, size_t n, hipStream_t s)
 // passes; 8-bit digits took 7 and were slower overall, 10-bit digits write
 // runs too short to coalesce), except that a sort takes some 10-bit digits
 // where they save a pass (56-bit keys: 6 passes, two of them 10-bit, not 7).
-// A fixed number of blocks each own a contiguous chunk of tiles (4096
+// At most a fixed number of blocks each own a contiguous chunk of tiles (1024 to 8192
 // keys).  Per pass:
 //   1. upsweep: digit histogram of each block's chunk -> hist[digit][block]
 //   2. exclusive scan of each digit's row of hist, and the rows' totals, from
@@ -331,21 +331,28 @@ void scan_u32_to_u64(const uint32_t *in, uint64_t *out, size_t n, hipStream_t s)
 
 namespace {
 
-constexpr int kSortBlock = 256;  // threads of an upsweep block
+constexpr int kSortBlock = 256;  // threads of a row's scan
 constexpr int kMaxRadixBits = 10;
 constexpr unsigned kMaxSortBlocks = 2048;
 
-// Shape of a downsweep tile: BLOCK threads of ROUNDS keys each.
-template <int BLOCK, int ROUNDS>
+// Shape of a downsweep tile: BLOCK threads of ROUNDS keys each; the upsweep's
+// threads, and the blocks of both at most.  The wide shape's downsweep has one
+// block per compute unit at a time, so 1024 blocks leave it four turns, and
+// half the counts of 2048 to write, scan and read (64e6 pairs: a pass 660 to
+// 642 us), with as many waves in the upsweep (1024 blocks of 256 threads took
+// 1.93 ms where 2048 took 1.51, 1024 of 1024 now 1.47).
+template <int BLOCK, int ROUNDS, int UP, unsigned BLOCKS>
 struct SortShape {
+    static constexpr int kUpBlock = UP;             // threads of an upsweep block
+    static constexpr unsigned kMaxBlocks = BLOCKS;
     static constexpr int kBlock = BLOCK;
     static constexpr int kRounds = ROUNDS;
     static constexpr int kWaves = BLOCK / kWave;
     static constexpr int kTile = BLOCK * ROUNDS;
 };
-using SortSmall = SortShape<256, 4>;
-using SortNarrow = SortShape<256, 16>;
-using SortWide = SortShape<1024, 8>;
+using SortSmall = SortShape<256, 4, 256, kMaxSortBlocks>;
+using SortNarrow = SortShape<256, 16, 256, kMaxSortBlocks>;
+using SortWide = SortShape<1024, 8, 1024, 1024>;
 
 template <int RB>
 __device__ __forceinline__ unsigned digit_of(uint64_t k, int shift)
@@ -353,25 +360,35 @@ __device__ __forceinline__ unsigned digit_of(uint64_t k, int shift)
     return (unsigned)(k >> shift) & ((1u << RB) - 1);
 }
 
+constexpr int kUpLoads = 8;  // keys in flight per thread of an upsweep
+
 // FEW: at most kFewBlocks blocks, whose counts leave as 32-bit words block by
 // block, for the downsweep to add up itself.
-template <class K, int RB, bool FEW>
-__global__ __launch_bounds__(kSortBlock) void radix_upsweep(const K *keys, size_t n, int shift, size_t chunk,
+template <class K, int RB, int BLOCK, bool FEW>
+__global__ __launch_bounds__(BLOCK) void radix_upsweep(const K *keys, size_t n, int shift, size_t chunk,
                                                             uint64_t *hist)
 {
     constexpr int kRadix = 1 << RB;
     __shared__ unsigned cnt[kRadix];
-    for (int d = threadIdx.x; d < kRadix; d += kSortBlock) cnt[d] = 0;
+    for (int d = threadIdx.x; d < kRadix; d += BLOCK) cnt[d] = 0;
     __syncthreads();
     const size_t lo = blockIdx.x * chunk;
     const size_t hi = std::min(n, lo + chunk);
-    for (size_t i = lo + threadIdx.x; i < hi; i += kSortBlock) atomicAdd(&cnt[digit_of<RB>(keys[i], shift)], 1u);
+    size_t i = lo + threadIdx.x;
+    for (; i + (size_t)(kUpLoads - 1) * BLOCK < hi; i += (size_t)kUpLoads * BLOCK) {
+        K k[kUpLoads];
+#pragma unroll
+        for (int j = 0; j < kUpLoads; ++j) k[j] = keys[i + (size_t)j * BLOCK];
+#pragma unroll
+        for (int j = 0; j < kUpLoads; ++j) atomicAdd(&cnt[digit_of<RB>(k[j], shift)], 1u);
+    }
+    for (; i < hi; i += BLOCK) atomicAdd(&cnt[digit_of<RB>(keys[i], shift)], 1u);
     __syncthreads();
     if (FEW) {
         uint32_t *few = reinterpret_cast<uint32_t *>(hist) + (size_t)blockIdx.x * kRadix;
-        for (int d = threadIdx.x; d < kRadix; d += kSortBlock) few[d] = cnt[d];
+        for (int d = threadIdx.x; d < kRadix; d += BLOCK) few[d] = cnt[d];
     } else {
-        for (int d = threadIdx.x; d < kRadix; d += kSortBlock) hist[(size_t)d * gridDim.x + blockIdx.x] = cnt[d];
+        for (int d = threadIdx.x; d < kRadix; d += BLOCK) hist[(size_t)d * gridDim.x + blockIdx.x] = cnt[d];
     }
 }
 
@@ -607,7 +624,7 @@ template <class K, int RB, class S, bool FEW>
 void sort_pass(const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, size_t n, int shift, unsigned nb, size_t tpb,
                uint64_t *hist, hipStream_t s)
 {
-    radix_upsweep<K, RB, FEW><<<nb, kSortBlock, 0, s>>>(ki, n, shift, tpb * S::kTile, hist);
+    radix_upsweep<K, RB, S::kUpBlock, FEW><<<nb, S::kUpBlock, 0, s>>>(ki, n, shift, tpb * S::kTile, hist);
     TP_CHECK_LAUNCH();
     if (!FEW) {
         radix_rows<<<1u << RB, kSortBlock, 0, s>>>(hist, nb);
@@ -625,7 +642,7 @@ bool radix_sort_shape(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, 
                       int begin_bit)
 {
     const size_t tiles = (n + S::kTile - 1) / S::kTile;
-    const unsigned nb = (unsigned)std::min<size_t>(tiles, kMaxSortBlocks);
+    const unsigned nb = (unsigned)std::min<size_t>(tiles, S::kMaxBlocks);
     const size_t tpb = (tiles + nb - 1) / nb;
     DArray<uint64_t> hist((size_t)(1u << kMaxRadixBits) * (nb + 1), s);  // the rows, then their totals
     // 9-bit digits, or as few 10-bit ones as cover `bits` in one pass less
