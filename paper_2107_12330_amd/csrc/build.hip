@@ -1066,12 +1066,29 @@ uint64_t graph_bytes(const tp_graph *g)
     return b;
 }
 
-// Cut the tiles of every class with the caps of `cfg` and record the plan's
-// statistics.  The work of each target (in-edges and wedge checks) is
-// recomputed from the in-edge index.
-void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
+namespace {
+
+// A plan that is cut, but not yet its graph's: whatever fails up to the wait
+// for its last kernel leaves the graph with the plan that it had.
+struct CutPlan {
+    PlanCfg cfg{};
+    DArray<TileDesc> tiles[kNumClasses], work_tiles[kNumClasses];
+    uint64_t n_tiles[kNumClasses] = {}, n_work_tiles[kNumClasses] = {};
+    // (empty where the graph has its piece records: they depend on the graph alone)
+    uint64_t n_piece_recs = 0;
+    DArray<uint64_t> piece_key;
+    DArray<uint32_t> piece_pay;
+    tp_graph_stats stats{};  // the graph's, with the plan's figures
+};
+
+// Cut the tiles of every class with the caps of `cfg`.  The work of each
+// target (in-edges and wedge checks) is recomputed from the in-edge index.
+// The plan is complete once `s` has been waited for.
+CutPlan cut_plan(const tp_graph *g, const PlanCfg &cfg, hipStream_t s)
 {
-    CallScope scope(s);
+    CutPlan plan;
+    plan.cfg = cfg;
+    plan.stats = g->stats;
     const uint32_t n = g->n;
     DArray<unsigned long long> work((size_t)n + kNumClasses, s);
     DArray<uint64_t> cptr((size_t)n + 1, s);
@@ -1093,9 +1110,6 @@ void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
     // (record, piece), laid out target by target and piece by piece; the
     // scan of the flags places every cut record
     DArray<uint64_t> fbase, pos;
-    g->piece_key.release();
-    g->piece_pay.release();
-    g->n_piece_recs = 0;
     if (g->n_in && g->stats.dplus_max > kLargeMaxDeg) {
         fbase.reset((size_t)n + 1, s);
         DArray<uint32_t> list(g->m / (kLargeMaxDeg + 1) + 1, s);
@@ -1124,14 +1138,14 @@ void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
             }
             scan_u32_to_u64(flag.get(), pos.get(), nf, s);
         }
-        const uint64_t nr = read_scalar(pos.get() + nf, s);
-        g->n_piece_recs = nr;
-        g->piece_key.reset(std::max<uint64_t>(nr, 1), s);
-        g->piece_pay.reset(std::max<uint64_t>(nr, 1), s);
+        const uint64_t nr = g->n_piece_recs ? 0 : read_scalar(pos.get() + nf, s);
         if (nr) {
+            plan.n_piece_recs = nr;
+            plan.piece_key.reset(nr, s);
+            plan.piece_pay.reset(nr, s);
             k_piece_cut<true><<<grid, kB, 0, s>>>(g->inkey.get(), g->inpay.get(), (int)g->kbits, list.get(), nh,
                                                   cptr.get(), g->rowptr.get(), g->col.get(), fbase.get(), nullptr,
-                                                  cut.get(), pos.get(), g->piece_key.get(), g->piece_pay.get());
+                                                  cut.get(), pos.get(), plan.piece_key.get(), plan.piece_pay.get());
             TP_CHECK_LAUNCH();
         }
     }
@@ -1156,30 +1170,60 @@ void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
     bool any = false;
     for (int c = 0; c < kNumClasses; ++c) {
         const uint64_t nt = total(kPlanTiles + c), nw = total(kPlanWork + c);
-        g->n_tiles[c] = nt;
-        g->tiles[c].reset(std::max<uint64_t>(nt, 1), s);
+        plan.n_tiles[c] = nt;
+        plan.tiles[c].reset(std::max<uint64_t>(nt, 1), s);
         // (a finer cut gives no target fewer tiles: as many in all is the same cut)
-        g->n_work_tiles[c] = nw == nt ? 0 : nw;
-        g->work_tiles[c].reset(g->n_work_tiles[c], s);
-        out.tiles[c] = nt ? g->tiles[c].get() : nullptr;
-        out.work[c] = g->work_tiles[c].get();
+        plan.n_work_tiles[c] = nw == nt ? 0 : nw;
+        plan.work_tiles[c].reset(plan.n_work_tiles[c], s);
+        out.tiles[c] = nt ? plan.tiles[c].get() : nullptr;
+        out.work[c] = plan.work_tiles[c].get();
         any = any || nt;
     }
     if (any) {
         k_plan_write<<<nb, kB, 0, s>>>(in, sums.get(), out);
         TP_CHECK_LAUNCH();
     }
-    g->stats.n_tiles = 0;
+    tp_graph_stats &st = plan.stats;
+    st.n_tiles = 0;
     for (int c = 0; c < kNumClasses; ++c) {
-        g->stats.class_tiles[c] = g->n_tiles[c];
-        g->stats.class_records[c] = total(kPlanRec + c);
-        g->stats.class_staged[c] = total(kPlanStaged + c);
-        g->stats.class_probes[c] = total(kPlanProbes + c);
-        g->stats.n_tiles += g->n_tiles[c];
+        st.class_tiles[c] = plan.n_tiles[c];
+        st.class_records[c] = total(kPlanRec + c);
+        st.class_staged[c] = total(kPlanStaged + c);
+        st.class_probes[c] = total(kPlanProbes + c);
+        st.n_tiles += plan.n_tiles[c];
     }
-    g->stats.probes = total(kPlanAll);
-    g->stats.n_targets = total(kPlanTargets);
-    g->plan = cfg;
+    st.probes = total(kPlanAll);
+    st.n_targets = total(kPlanTargets);
+    return plan;
+}
+
+// Make a complete plan the graph's.  Nothing here can fail.
+void adopt_plan(tp_graph *g, CutPlan &plan)
+{
+    for (int c = 0; c < kNumClasses; ++c) {
+        g->tiles[c] = std::move(plan.tiles[c]);
+        g->work_tiles[c] = std::move(plan.work_tiles[c]);
+        g->n_tiles[c] = plan.n_tiles[c];
+        g->n_work_tiles[c] = plan.n_work_tiles[c];
+    }
+    if (plan.n_piece_recs) {
+        g->n_piece_recs = plan.n_piece_recs;
+        g->piece_key = std::move(plan.piece_key);
+        g->piece_pay = std::move(plan.piece_pay);
+    }
+    g->plan = plan.cfg;
+    g->stats = plan.stats;
+    g->stats.device_bytes = graph_bytes(g);
+}
+
+}  // namespace
+
+void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s)
+{
+    CallScope scope(s);
+    CutPlan plan = cut_plan(g, cfg, s);
+    TP_HIP(hipStreamSynchronize(s));
+    adopt_plan(g, plan);
 }
 
 // ================================================================ build
@@ -1488,9 +1532,10 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
     TP_HIP(hipStreamSynchronize(s));
     g->n_in = hs[6];
     g->stats.dplus_max = hs[5];  // the plan cuts huge targets' records
-    plan_graph(g.get(), cfg, s);
+    CutPlan plan = cut_plan(g.get(), cfg, s);
     TP_HIP(hipEventRecord(ev[8], s));
     TP_HIP(hipStreamSynchronize(s));
+    adopt_plan(g.get(), plan);
 
     g->stats.n_vertices = n;
     g->stats.wedges = hs[4];
@@ -1506,7 +1551,6 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
         total += t;
     }
     g->stats.build_ms = total;
-    g->stats.device_bytes = graph_bytes(g.get());
     *out = g.release();
 }
 

@@ -76,7 +76,8 @@ struct tp_graph {
 };
 
 // Cut the survey tiles of every class with the caps of `cfg`, store `cfg` as
-// the graph's plan and refresh the plan statistics (build.hip).
+// the graph's plan and refresh the plan statistics (build.hip).  Waits for
+// `s`; where it fails, the graph keeps the plan that it had.
 void plan_graph(tp_graph *g, const PlanCfg &cfg, hipStream_t s);
 
 // Device bytes held by a graph.

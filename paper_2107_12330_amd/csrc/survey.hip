@@ -2923,75 +2923,91 @@ extern "C" tp_status tripoll_set_plan(tp_graph *g, const tp_plan *plan, void *st
         if (!g || !plan) fail(TP_ERR_INVALID, "tripoll_set_plan: NULL argument");
         check_plan(plan);
         plan_graph(g, to_cfg(plan), (hipStream_t)stream);
-        g->stats.device_bytes = graph_bytes(g);
     });
 }
+
+namespace {
+
+void tune(tp_graph *g, const tp_survey_spec *spec, hipStream_t s, tp_tune_result *out)
+{
+    tp_survey_spec sp = *spec;
+    sp.strategy = TP_STRAT_AUTO;
+    DArray<unsigned long long> buf(TP_RESULT_WORDS, s);
+    zero_u64<<<grid_for(TP_RESULT_WORDS, 256), 256, 0, s>>>(buf.get(), TP_RESULT_WORDS);
+    TP_CHECK_LAUNCH();
+    static const uint32_t kCaps[] = {256, 1024, 4096, 16384};
+    static const std::vector<uint32_t> kCands[kNumClasses] = {
+        {TP_VAR_WAVE_TABLE, TP_VAR_GROUP_TABLE, TP_VAR_WAVE_SEARCH},
+        {TP_VAR_GROUP_TABLE, TP_VAR_SEARCH, TP_VAR_WAVE_SEARCH},
+        {TP_VAR_GROUP_TABLE, TP_VAR_SEARCH},
+        {TP_VAR_GROUP_TABLE, TP_VAR_SEARCH}};
+    tp_tune_result r{};
+    float best[kNumClasses];
+    uint32_t best_v[kNumClasses], best_cap[kNumClasses];
+    for (int c = 0; c < kNumClasses; ++c) {
+        best[c] = -1.f;
+        best_v[c] = TP_VAR_DEFAULT;
+        best_cap[c] = default_tile_records(c);
+    }
+    for (uint32_t cap : kCaps) {
+        PlanCfg cfg{};
+        for (int c = 0; c < kNumClasses; ++c) cfg.tile_records[c] = cap;
+        plan_graph(g, cfg, s);
+        for (int c = 0; c < kNumClasses; ++c) {
+            if (g->n_tiles[c] == 0) continue;
+            const uint32_t dflt = resolve_variant(g, c, TP_STRAT_AUTO);
+            for (uint32_t v : kCands[c]) {
+                // a warm-up launch, then the faster of two timed ones
+                (void)time_class(g, &sp, buf.get(), c, v, 1, s);
+                const float ms = time_class(g, &sp, buf.get(), c, v, 2, s);
+                ++r.trials;
+                if (cap == default_tile_records(c) && v == dflt) r.default_ms[c] = ms;
+                if (best[c] < 0.f || ms < best[c]) {
+                    best[c] = ms;
+                    best_v[c] = v;
+                    best_cap[c] = cap;
+                }
+            }
+        }
+    }
+    // keep the default unless the best is clearly faster
+    PlanCfg fin{};
+    for (int c = 0; c < kNumClasses; ++c) {
+        fin.variant[c] = TP_VAR_DEFAULT;
+        fin.tile_records[c] = default_tile_records(c);
+        if (best[c] >= 0.f && best[c] < 0.97f * r.default_ms[c]) {
+            fin.variant[c] = best_v[c];
+            fin.tile_records[c] = best_cap[c];
+        }
+    }
+    plan_graph(g, fin, s);
+    for (int c = 0; c < kNumClasses; ++c) {
+        r.chosen.variant[c] = fin.variant[c];
+        r.chosen.tile_records[c] = fin.tile_records[c];
+        r.tuned_ms[c] = g->n_tiles[c] ? time_class(g, &sp, buf.get(), c, resolve_variant(g, c, TP_STRAT_AUTO), 2, s)
+                                      : 0.f;
+    }
+    TP_HIP(hipStreamSynchronize(s));
+    *out = r;
+}
+
+}  // namespace
 
 extern "C" tp_status tripoll_tune(tp_graph *g, const tp_survey_spec *spec, void *stream, tp_tune_result *out)
 {
     return guard([&] {
         if (!out) fail(TP_ERR_INVALID, "tripoll_tune: NULL result");
         validate_spec(g, spec);
-        hipStream_t s = (hipStream_t)stream;
-        tp_survey_spec sp = *spec;
-        sp.strategy = TP_STRAT_AUTO;
-        DArray<unsigned long long> buf(TP_RESULT_WORDS, s);
-        zero_u64<<<grid_for(TP_RESULT_WORDS, 256), 256, 0, s>>>(buf.get(), TP_RESULT_WORDS);
-        TP_CHECK_LAUNCH();
-        static const uint32_t kCaps[] = {256, 1024, 4096, 16384};
-        static const std::vector<uint32_t> kCands[kNumClasses] = {
-            {TP_VAR_WAVE_TABLE, TP_VAR_GROUP_TABLE, TP_VAR_WAVE_SEARCH},
-            {TP_VAR_GROUP_TABLE, TP_VAR_SEARCH, TP_VAR_WAVE_SEARCH},
-            {TP_VAR_GROUP_TABLE, TP_VAR_SEARCH},
-            {TP_VAR_GROUP_TABLE, TP_VAR_SEARCH}};
-        tp_tune_result r{};
-        float best[kNumClasses];
-        uint32_t best_v[kNumClasses], best_cap[kNumClasses];
-        for (int c = 0; c < kNumClasses; ++c) {
-            best[c] = -1.f;
-            best_v[c] = TP_VAR_DEFAULT;
-            best_cap[c] = default_tile_records(c);
-        }
-        for (uint32_t cap : kCaps) {
-            PlanCfg cfg{};
-            for (int c = 0; c < kNumClasses; ++c) cfg.tile_records[c] = cap;
-            plan_graph(g, cfg, s);
-            for (int c = 0; c < kNumClasses; ++c) {
-                if (g->n_tiles[c] == 0) continue;
-                const uint32_t dflt = resolve_variant(g, c, TP_STRAT_AUTO);
-                for (uint32_t v : kCands[c]) {
-                    // a warm-up launch, then the faster of two timed ones
-                    (void)time_class(g, &sp, buf.get(), c, v, 1, s);
-                    const float ms = time_class(g, &sp, buf.get(), c, v, 2, s);
-                    ++r.trials;
-                    if (cap == default_tile_records(c) && v == dflt) r.default_ms[c] = ms;
-                    if (best[c] < 0.f || ms < best[c]) {
-                        best[c] = ms;
-                        best_v[c] = v;
-                        best_cap[c] = cap;
-                    }
-                }
+        const PlanCfg before = g->plan;
+        try {
+            tune(g, spec, (hipStream_t)stream, out);
+        } catch (...) {
+            // not left with one of the trials where its own plan can be cut again
+            try {
+                if (std::memcmp(&g->plan, &before, sizeof(before)) != 0) plan_graph(g, before, (hipStream_t)stream);
+            } catch (...) {
             }
+            throw;
         }
-        // keep the default unless the best is clearly faster
-        PlanCfg fin{};
-        for (int c = 0; c < kNumClasses; ++c) {
-            fin.variant[c] = TP_VAR_DEFAULT;
-            fin.tile_records[c] = default_tile_records(c);
-            if (best[c] >= 0.f && best[c] < 0.97f * r.default_ms[c]) {
-                fin.variant[c] = best_v[c];
-                fin.tile_records[c] = best_cap[c];
-            }
-        }
-        plan_graph(g, fin, s);
-        g->stats.device_bytes = graph_bytes(g);
-        for (int c = 0; c < kNumClasses; ++c) {
-            r.chosen.variant[c] = fin.variant[c];
-            r.chosen.tile_records[c] = fin.tile_records[c];
-            r.tuned_ms[c] = g->n_tiles[c] ? time_class(g, &sp, buf.get(), c, resolve_variant(g, c, TP_STRAT_AUTO), 2, s)
-                                          : 0.f;
-        }
-        TP_HIP(hipStreamSynchronize(s));
-        *out = r;
     });
 }
