@@ -5,8 +5,8 @@
 #include <atomic>
 #include <map>
 #include <mutex>
-#include <unordered_map>
 
+#include "pool.hpp"
 #include "tp_internal.hpp"
 
 namespace tp {
@@ -24,12 +24,22 @@ const char *last_error_cstr() { return g_last_error.c_str(); }
 
 namespace {
 
-struct Pool {
-    std::mutex mu;
-    std::multimap<size_t, void *> free_blocks;        // size -> block
-    std::unordered_map<void *, size_t> live;          // block -> size
-    size_t cached = 0;
+struct HipDevice {
+    using Stream = hipStream_t;
+    void *take(size_t bytes)
+    {
+        void *p = nullptr;
+        const hipError_t e = hipMalloc(&p, bytes);
+        if (e == hipSuccess) return p;
+        (void)hipGetLastError();
+        if (e != hipErrorOutOfMemory && e != hipErrorMemoryAllocation)
+            fail(TP_ERR_DEVICE, "device allocation of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e));
+        return nullptr;
+    }
+    void give(void *p) { (void)hipFree(p); }
+    void wait(hipStream_t s) { (void)hipStreamSynchronize(s); }
 };
+using Pool = BlockPool<HipDevice>;
 
 Pool &pool_for_current_device()
 {
@@ -43,18 +53,7 @@ Pool &pool_for_current_device()
     return *p;
 }
 
-size_t round_size(size_t bytes)
-{
-    const size_t small = 512, big = size_t(2) << 20;
-    return bytes < big ? (bytes + small - 1) / small * small : (bytes + big - 1) / big * big;
-}
-
-void trim_locked(Pool &p)
-{
-    for (auto &kv : p.free_blocks) (void)hipFree(kv.second);
-    p.free_blocks.clear();
-    p.cached = 0;
-}
+thread_local Pool::Scope t_scope;
 
 // Fault injection: when non-zero, the allocation that brings it to zero
 // fails as if the device were out of memory.
@@ -64,53 +63,14 @@ std::atomic<uint64_t> g_fail_countdown{0};
 
 void dev_fail_after(uint64_t n) { g_fail_countdown.store(n); }
 
-// ---- the calling thread's scope
-
-namespace {
-
-struct Scope {
-    bool on = false;
-    hipStream_t stream = nullptr;
-    std::multimap<size_t, void *> blocks;  // released in the scope, by size; still live in the pool
-};
-thread_local Scope t_scope;
-
-// A cached block may stand in for a request that is not much smaller.
-bool fits(size_t block, size_t sz) { return block <= sz + sz / 4 + (size_t(8) << 20); }
-
-// Wait for the scope's stream and hand its blocks to the pool's cache.
-void scope_flush(Scope &sc)
+CallScope::CallScope(hipStream_t stream) : outer_(!t_scope.pool)
 {
-    if (sc.blocks.empty()) return;
-    (void)hipStreamSynchronize(sc.stream);
-    Pool &p = pool_for_current_device();
-    std::lock_guard<std::mutex> lk(p.mu);
-    for (auto &kv : sc.blocks) {
-        if (!p.live.erase(kv.second)) continue;
-        p.free_blocks.emplace(kv.first, kv.second);
-        p.cached += kv.first;
-    }
-    sc.blocks.clear();
-}
-
-}  // namespace
-
-CallScope::CallScope(hipStream_t stream) : outer_(!t_scope.on)
-{
-    if (!outer_) return;
-    t_scope.on = true;
-    t_scope.stream = stream;
+    if (outer_) pool_for_current_device().open(t_scope, stream);
 }
 
 CallScope::~CallScope()
 {
-    if (!outer_) return;
-    t_scope.on = false;
-    try {
-        scope_flush(t_scope);
-    } catch (...) {
-        t_scope.blocks.clear();  // no current device: the blocks stay counted as live
-    }
+    if (outer_) t_scope.pool->close(t_scope);
 }
 
 void *dev_alloc(size_t bytes, hipStream_t stream)
@@ -121,89 +81,21 @@ void *dev_alloc(size_t bytes, hipStream_t stream)
             break;
         }
     }
-    Pool &p = pool_for_current_device();
-    const size_t sz = round_size(bytes ? bytes : 1);
-    if (t_scope.on && stream == t_scope.stream) {
-        auto own = t_scope.blocks.lower_bound(sz);
-        if (own != t_scope.blocks.end() && fits(own->first, sz)) {
-            void *ptr = own->second;
-            t_scope.blocks.erase(own);
-            return ptr;
-        }
-    }
-    std::unique_lock<std::mutex> lk(p.mu);
-    auto it = p.free_blocks.lower_bound(sz);
-    // reuse a cached block when it is not much larger than the request
-    if (it != p.free_blocks.end() && fits(it->first, sz)) {
-        void *ptr = it->second;
-        p.live[ptr] = it->first;
-        p.cached -= it->first;
-        p.free_blocks.erase(it);
-        return ptr;
-    }
-    void *ptr = nullptr;
-    hipError_t e = hipMalloc(&ptr, sz);
-    if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-        (void)hipGetLastError();
-        if (t_scope.on) {
-            lk.unlock();
-            scope_flush(t_scope);
-            lk.lock();
-        }
-        trim_locked(p);
-        e = hipMalloc(&ptr, sz);
-    }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        fail(e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation ? TP_ERR_OOM : TP_ERR_DEVICE,
-             "device allocation of " + std::to_string(sz) + " bytes failed: " + hipGetErrorString(e));
-    }
-    p.live[ptr] = sz;
-    return ptr;
+    void *p = pool_for_current_device().alloc(bytes, stream, &t_scope);
+    if (!p) fail(TP_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes failed: out of memory");
+    return p;
 }
 
 void dev_release(void *ptr, hipStream_t stream)
 {
-    if (!ptr) return;
-    Pool &p = pool_for_current_device();
-    if (t_scope.on && stream == t_scope.stream) {
-        std::lock_guard<std::mutex> lk(p.mu);
-        auto it = p.live.find(ptr);
-        if (it != p.live.end()) t_scope.blocks.emplace(it->second, ptr);
-        return;
-    }
-    // the block may still be in use by work on `stream`
-    (void)hipStreamSynchronize(stream);
-    std::lock_guard<std::mutex> lk(p.mu);
-    auto it = p.live.find(ptr);
-    if (it == p.live.end()) return;
-    p.free_blocks.emplace(it->second, ptr);
-    p.cached += it->second;
-    p.live.erase(it);
+    if (ptr) pool_for_current_device().release(ptr, stream, &t_scope);
 }
 
-void dev_trim()
-{
-    Pool &p = pool_for_current_device();
-    std::lock_guard<std::mutex> lk(p.mu);
-    trim_locked(p);
-}
+void dev_trim() { pool_for_current_device().trim(); }
 
-size_t dev_cached_bytes()
-{
-    Pool &p = pool_for_current_device();
-    std::lock_guard<std::mutex> lk(p.mu);
-    return p.cached;
-}
+size_t dev_cached_bytes() { return pool_for_current_device().cached(); }
 
-size_t dev_live_bytes()
-{
-    Pool &p = pool_for_current_device();
-    std::lock_guard<std::mutex> lk(p.mu);
-    size_t b = 0;
-    for (const auto &kv : p.live) b += kv.second;
-    return b;
-}
+size_t dev_live_bytes() { return pool_for_current_device().live(); }
 
 // ================================================================ fill
 

@@ -58,12 +58,13 @@ tp_status guard(F &&body)
 
 // ---------------------------------------------------------------- memory
 
-// Caching device allocator: blocks obtained from hipMalloc are kept after
-// release and handed out again for requests of similar size, so repeated
-// builds do not pay for page mapping.  On an allocation failure the cache is
-// returned to the driver and the request retried once.  Release is
-// synchronous with respect to `stream` so a cached block is never handed out
-// while a kernel may still touch it.
+// Caching device allocator (pool.hpp): blocks obtained from hipMalloc are
+// kept after release and handed out again for requests of similar size, so
+// repeated builds do not pay for page mapping.  On an allocation failure all
+// released blocks of the device, those held by other threads' calls among
+// them, are returned to the driver and the request is retried once.  A release
+// waits for `stream`, so that a cached block is never handed out while a
+// kernel may still touch it, but for a CallScope's.
 void *dev_alloc(size_t bytes, hipStream_t stream);
 void dev_release(void *p, hipStream_t stream);
 void dev_trim();
@@ -72,12 +73,14 @@ size_t dev_live_bytes();   // bytes handed out and not yet released
 void dev_fail_after(uint64_t n);  // fault injection: the n-th allocation from now fails (0: off)
 
 // While a CallScope exists on a thread, the blocks that the thread releases
-// with the scope's stream are kept for its own later allocations, which are
+// with the scope's stream are held for its own later allocations, which are
 // used by work on the same stream and so after the work that still touches
 // the block: neither side waits.  When the scope ends it waits for the stream
 // once and gives the blocks to the cache.  Library calls that work on one
 // stream and end synchronously hold one (a small build released some 25
-// temporaries, a wait of 10 to 20 us each); inside another one it does nothing.
+// temporaries, a wait of 10 to 20 us each); inside another one it does
+// nothing.  (The wait reports no error: a call whose results depend on it
+// waits itself.)
 class CallScope {
 public:
     explicit CallScope(hipStream_t stream);
