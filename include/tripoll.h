@@ -113,7 +113,7 @@ typedef struct {
     uint64_t probes;           /* wedge checks the survey issues (|W+| minus wedges whose
                                   middle vertex has no out-edge, which cannot close) */
     uint64_t n_targets;        /* vertices q with at least one wedge to check */
-    uint64_t n_tiles;          /* work tiles of the survey plan */
+    uint64_t n_tiles;          /* tiles that a survey walks under the plan */
     uint64_t device_bytes;     /* HBM held by the graph */
     uint32_t max_label;
     uint32_t reserved;
@@ -530,7 +530,11 @@ tp_status tripoll_launch_free(tp_launch *launch);
  * (TP_VAR_*) and the cap on in-edge records per tile (a tile is the unit of
  * work one workgroup or wave claims; a target with more records, or more
  * than 256 wedge checks per record of cap, is cut into several interleaved
- * tiles).  Results never depend on the plan, only the time does.
+ * tiles).  Under its default cap (1024; 16384 for the large and huge classes)
+ * a class with too few records to keep the device busy is cut finer, into
+ * about 8 tiles (4) for everything that claims them; any other cap is walked
+ * as it is.  The streamed enumeration always walks the plan's own tiles.
+ * Results never depend on the plan, only the time does.
  *   tile_records  power of two in [16, 65536]
  */
 typedef struct {
@@ -543,7 +547,9 @@ tp_status tripoll_get_plan(const tp_graph *g, tp_plan *out);
 
 /*
  * Replace the plan of a graph (re-cuts the tiles on `stream`; synchronous).
- * Not to be called while surveys of the graph are in flight.
+ * Not to be called while surveys of the graph are in flight.  The tiles of both
+ * plans are held until the new ones are complete; a call that fails leaves the
+ * graph with the plan that it had.
  * Errors: TP_ERR_INVALID for an unknown variant, a variant the class cannot
  * use (per-wave tables outside the tiny class) or
  * a tile cap that is not a power of two in [16, 65536].
@@ -563,7 +569,7 @@ typedef struct {
  * Autotune the plan for one survey kind: for every class, time each usable
  * variant at tile caps 256, 1024, 4096 and 16384 with the survey `spec` on
  * this graph, and keep the fastest per class (the default -- the class's own
- * variant, 1024 records per tile, 16384 for the large class -- stays unless
+ * variant under its default cap, cut finer on small graphs -- stays unless
  * another beats it by more than 3%).  Runs real surveys (cost: a few times one
  * survey).  Synchronous; sets the plan on the graph.  Not to be called while
  * surveys of the graph are in flight.

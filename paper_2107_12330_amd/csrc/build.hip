@@ -696,8 +696,8 @@ __device__ __forceinline__ uint32_t tiles_of(uint64_t cnt, uint64_t work, uint32
     return (uint32_t)t;
 }
 
-// The caps of the work tiles (the cut the surveys walk): where a class has
-// too little work to give every claimer of a full device about 8 tiles (4 in
+// The caps of the work tiles (the cut the surveys walk): where a class whose
+// cap is the default one has too little work to give every claimer of a full device about 8 tiles (4 in
 // the larger two classes) at the plan's cap, its records are cut finer, down to a floor
 // below which a tile's table and claim would outweigh its records.  The
 // claimers are waves for the tiny class and workgroups for the others, as
@@ -787,7 +787,8 @@ __device__ __forceinline__ void class_caps(const PlanIn &in, int c, uint32_t &rc
             wc = in.caps.work[i];
         }
     }
-    frc = work_rec_cap(c, rc, in.rec[c]);
+    // (a cap that a caller has chosen is walked as it is)
+    frc = rc == default_tile_records(c) ? work_rec_cap(c, rc, in.rec[c]) : rc;
     fwc = min(wc, kTileWorkPerRecord * (uint64_t)frc);
 }
 
@@ -830,8 +831,8 @@ __global__ __launch_bounds__(kB) void k_plan_count(PlanIn in, uint64_t *sums /* 
         const PlanTarget t = plan_target(in, q);
         if (!t.cnt) continue;
         // a huge target: the records cut to its pieces, each piece staged by
-        // each of its tiles
-        uint64_t nrec = t.cnt, staged = (uint64_t)t.tiles * t.dq;
+        // each of its tiles (the ones that surveys walk)
+        uint64_t nrec = t.cnt, staged = (uint64_t)t.work_tiles * t.dq;
         if (t.c == kClassHuge) {
             uint32_t rc, frc;
             uint64_t wc, fwc;
@@ -843,7 +844,7 @@ __global__ __launch_bounds__(kB) void k_plan_count(PlanIn in, uint64_t *sums /* 
                 uint64_t first, count;
                 piece_records(in.fbase, in.pos, q, j, t.cnt, first, count);
                 nrec += count;
-                staged += (uint64_t)tiles_of(count, (t.work + S - 1) / S, rc, wc) *
+                staged += (uint64_t)tiles_of(count, (t.work + S - 1) / S, frc, fwc) *
                           min((uint64_t)psz, t.dq - (uint64_t)j * psz);
             }
         }
@@ -1186,11 +1187,11 @@ CutPlan cut_plan(const tp_graph *g, const PlanCfg &cfg, hipStream_t s)
     tp_graph_stats &st = plan.stats;
     st.n_tiles = 0;
     for (int c = 0; c < kNumClasses; ++c) {
-        st.class_tiles[c] = plan.n_tiles[c];
+        st.class_tiles[c] = plan.n_work_tiles[c] ? plan.n_work_tiles[c] : plan.n_tiles[c];
         st.class_records[c] = total(kPlanRec + c);
         st.class_staged[c] = total(kPlanStaged + c);
         st.class_probes[c] = total(kPlanProbes + c);
-        st.n_tiles += plan.n_tiles[c];
+        st.n_tiles += st.class_tiles[c];
     }
     st.probes = total(kPlanAll);
     st.n_targets = total(kPlanTargets);

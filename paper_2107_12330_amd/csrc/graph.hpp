@@ -65,8 +65,8 @@ struct tp_graph {
     tp::DArray<uint32_t> rank_gid; // [n] graph of each rank (batches only)
     uint64_t n_tiles[kNumClasses] = {};
     // the finer cut of the same records that the surveys walk where the
-    // tiles are too few to fill the device (n_work_tiles 0: the tiles
-    // themselves); the streamed enumeration keeps the tiles
+    // default cap's tiles are too few to fill the device (n_work_tiles 0: the
+    // tiles themselves); the streamed enumeration keeps the tiles
     tp::DArray<TileDesc> work_tiles[kNumClasses];
     uint64_t n_work_tiles[kNumClasses] = {};
     const TileDesc *survey_tiles(int c) const { return n_work_tiles[c] ? work_tiles[c].get() : tiles[c].get(); }

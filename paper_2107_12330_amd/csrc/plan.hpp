@@ -47,10 +47,10 @@ __host__ __device__ inline uint32_t piece_size(uint64_t dq)
 // others.
 constexpr uint32_t kTileRecords = 1024;
 constexpr uint64_t kTileWorkPerRecord = 256;
-inline uint32_t default_tile_records(int cls) { return cls >= 2 ? 16384u : kTileRecords; }
+__host__ __device__ inline uint32_t default_tile_records(int cls) { return cls >= 2 ? 16384u : kTileRecords; }
 
-// Fewest records of a work tile's cap (the finer cut of graphs too small to
-// fill the device) in the tiny, the small and the two larger classes, whose
+// Fewest records of a work tile's cap (the finer cut, under the default cap, of
+// graphs too small to fill the device) in the tiny, the small and the two larger classes, whose
 // tables take longer to fill.  16 against 32 for the tiny class: scale 13 44
 // against 53 us, 300,007 vertices 156 against 147 us; 16 for the small class:
 // 73 against 57 us at scale 13.
