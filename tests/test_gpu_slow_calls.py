@@ -1,0 +1,56 @@
+"""Calls that must not take many times what comparable work on the same graph
+takes: the times of two calls are compared in one run, each the least of
+several, with a margin on their ordinary ratio."""
+import time
+
+import numpy as np
+import pytest
+
+from paper_2107_12330_amd import tripoll as tp
+from tests.graphs import huge_targets
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def T():
+    import torch
+    assert torch.cuda.is_available()
+    torch.cuda.set_device(0)
+    return torch
+
+
+def least(T, call, reps=7):
+    call()
+    best = 1e9
+    for _ in range(reps):
+        T.cuda.synchronize()
+        t0 = time.perf_counter()
+        call()
+        T.cuda.synchronize()
+        best = min(best, time.perf_counter() - t0)
+    return best * 1e3
+
+
+@pytest.fixture(scope="module")
+def hubs(T):
+    """3400 tiny targets of 2900 records each, most of them from leaves (and 40
+    huge ones, whose rows make long records of the tiny targets)."""
+    n, *edges = huge_targets(3)
+    with tp.build_graph(n, *(T.from_numpy(x).cuda() for x in edges)) as G:
+        yield G
+
+
+def tiny_ms(T, G, cap):
+    tp.tripoll_set_plan(G.handle, tp.make_plan((0,) * 4, (cap, 1024, 16384, 16384)))
+    T.cuda.synchronize()
+    ms = min(tp.survey(G)["class_ms"][0] for _ in range(9))
+    print("cap", cap, G.stats()["class_tiles"], "%.3f ms" % ms, flush=True)
+    return ms
+
+
+def test_few_large_tiles_fill_the_device(T, hubs):
+    """Tiles for fewer waves than the device holds: every workgroup that is
+    launched gets some (in blocks of eight tiles half of them got none: twice
+    the time of smaller tiles)."""
+    assert tiny_ms(T, hubs, 2048) < 1.5 * tiny_ms(T, hubs, 512)
