@@ -707,13 +707,41 @@ __device__ __forceinline__ uint32_t tiles_of(uint64_t cnt, uint64_t work, uint32
 // 8 tiles against 4: 300-graph batch's tiny class 1.63 against 2.07 ms, 300,007
 // vertices' small class 407 against 467 us, scale 22's large class 2.71
 // against 2.63 ms.
+__host__ __device__ inline uint64_t class_claimers(int c)
+{
+    return c == kClassTiny ? 256 * 32 : (c == kClassSmall ? 256 * 5 : 256);
+}
+
 __device__ __forceinline__ uint32_t work_rec_cap(int c, uint32_t rec_cap, uint64_t class_records)
 {
     const uint64_t share = c == kClassTiny || c == kClassSmall ? 8 : 4;
-    const uint64_t claimers = c == kClassTiny ? 256 * 32 : (c == kClassSmall ? 256 * 5 : 256);
+    const uint64_t claimers = class_claimers(c);
     const uint32_t least = c == kClassTiny ? kWorkRecMinTiny : (c == kClassSmall ? kWorkRecMinSmall : kWorkRecMinLarge);
     const uint64_t want = class_records / (claimers * share);
     return (uint32_t)min((uint64_t)rec_cap, max((uint64_t)least, want));
+}
+
+// Whether a class is cut finer after all, given its records, its tiles at the
+// plan's cap and the finer ones: not into more than four times as many, where
+// the plan's tiles are as many as an eighth of the claimers.  That is where few
+// targets hold most of the records, hubs of leaves.  Every finer tile fills
+// its target's table again (331,000 records of hubs with d+ of some 700, small
+// class: 477 tiles 63 us, 10,555 tiles 180 us), and since the tiles of a target
+// interleave, each walks the whole range of its rows, which the targets walked
+// at the same time share in cache (10e6 records of hubs with d+ of 17, tiny
+// class, count and survey: 11,250 tiles 515 and 925 us, 67,304 tiles 1012 and
+// 1397).  The tiny class's tables are filled by a wave in one round, and up to
+// 2^20 records its finer tiles are the faster ones (542,000: 128 against 97 us
+// of count and 179 against 110 of survey; 1,376,000: 90 against 151 and 140
+// against 169).  R-MAT graphs are cut into at most 2.8 (tiny) and 4.5 (small)
+// times as many: at 4.2 and 4.5 the small class took 48 and 139 us uncut,
+// 57 and 171 cut.
+constexpr uint64_t kFinerMost = 4;
+constexpr uint64_t kFinerTinyRecords = uint64_t(1) << 20;
+bool cut_finer(int c, uint64_t records, uint64_t tiles, uint64_t finer)
+{
+    return finer <= kFinerMost * tiles || 8 * tiles < class_claimers(c) ||
+           (c == kClassTiny && records < kFinerTinyRecords);
 }
 
 // Records of piece j of target q (pieces of huge targets; pos[] is the
@@ -752,12 +780,12 @@ __global__ __launch_bounds__(kB) void k_plan_records(const uint32_t *incnt, cons
 constexpr int kPlanItems = 2;
 constexpr size_t kPlanChunk = (size_t)kB * kPlanItems;
 // rows: tiles and work tiles of each class (target order), then records,
-// staged out-list entries and wedge checks of each class, then all wedge
-// checks and the targets with any
-static_assert(5 * kNumClasses + 2 < kWave, "k_plan_heads takes one lane per row");
+// staged out-list entries under either cut and wedge checks of each class, then
+// all wedge checks and the targets with any
+static_assert(6 * kNumClasses + 2 < kWave, "k_plan_heads takes one lane per row");
 constexpr int kPlanTiles = 0, kPlanWork = kNumClasses, kPlanRec = 2 * kNumClasses, kPlanStaged = 3 * kNumClasses,
-              kPlanProbes = 4 * kNumClasses, kPlanAll = 5 * kNumClasses, kPlanTargets = 5 * kNumClasses + 1,
-              kPlanRows = 5 * kNumClasses + 2;
+              kPlanWorkStaged = 4 * kNumClasses, kPlanProbes = 5 * kNumClasses, kPlanAll = 6 * kNumClasses,
+              kPlanTargets = 6 * kNumClasses + 1, kPlanRows = 6 * kNumClasses + 2;
 
 struct PlanIn {
     const uint64_t *cptr;             // [n + 1] first record of each target
@@ -831,8 +859,8 @@ __global__ __launch_bounds__(kB) void k_plan_count(PlanIn in, uint64_t *sums /* 
         const PlanTarget t = plan_target(in, q);
         if (!t.cnt) continue;
         // a huge target: the records cut to its pieces, each piece staged by
-        // each of its tiles (the ones that surveys walk)
-        uint64_t nrec = t.cnt, staged = (uint64_t)t.work_tiles * t.dq;
+        // each of its tiles
+        uint64_t nrec = t.cnt, staged = (uint64_t)t.tiles * t.dq, work_staged = (uint64_t)t.work_tiles * t.dq;
         if (t.c == kClassHuge) {
             uint32_t rc, frc;
             uint64_t wc, fwc;
@@ -840,12 +868,14 @@ __global__ __launch_bounds__(kB) void k_plan_count(PlanIn in, uint64_t *sums /* 
             const uint32_t S = piece_count(t.dq), psz = piece_size(t.dq);
             nrec = 0;
             staged = 0;
+            work_staged = 0;
             for (uint32_t j = 0; j < S; ++j) {
                 uint64_t first, count;
                 piece_records(in.fbase, in.pos, q, j, t.cnt, first, count);
                 nrec += count;
-                staged += (uint64_t)tiles_of(count, (t.work + S - 1) / S, frc, fwc) *
-                          min((uint64_t)psz, t.dq - (uint64_t)j * psz);
+                const uint64_t keys = min((uint64_t)psz, t.dq - (uint64_t)j * psz);
+                staged += tiles_of(count, (t.work + S - 1) / S, rc, wc) * keys;
+                work_staged += tiles_of(count, (t.work + S - 1) / S, frc, fwc) * keys;
             }
         }
 #pragma unroll
@@ -855,6 +885,7 @@ __global__ __launch_bounds__(kB) void k_plan_count(PlanIn in, uint64_t *sums /* 
             v[kPlanWork + i] += on ? t.work_tiles : 0u;
             v[kPlanRec + i] += on && t.tiles ? nrec : 0u;
             v[kPlanStaged + i] += on && t.tiles ? staged : 0u;
+            v[kPlanWorkStaged + i] += on && t.tiles ? work_staged : 0u;
             v[kPlanProbes + i] += on && t.tiles ? t.work : 0u;
         }
         v[kPlanAll] += t.work;
@@ -1174,7 +1205,7 @@ CutPlan cut_plan(const tp_graph *g, const PlanCfg &cfg, hipStream_t s)
         plan.n_tiles[c] = nt;
         plan.tiles[c].reset(std::max<uint64_t>(nt, 1), s);
         // (a finer cut gives no target fewer tiles: as many in all is the same cut)
-        plan.n_work_tiles[c] = nw == nt ? 0 : nw;
+        plan.n_work_tiles[c] = nw == nt || !cut_finer(c, total(kPlanRec + c), nt, nw) ? 0 : nw;
         plan.work_tiles[c].reset(plan.n_work_tiles[c], s);
         out.tiles[c] = nt ? plan.tiles[c].get() : nullptr;
         out.work[c] = plan.work_tiles[c].get();
@@ -1189,7 +1220,7 @@ CutPlan cut_plan(const tp_graph *g, const PlanCfg &cfg, hipStream_t s)
     for (int c = 0; c < kNumClasses; ++c) {
         st.class_tiles[c] = plan.n_work_tiles[c] ? plan.n_work_tiles[c] : plan.n_tiles[c];
         st.class_records[c] = total(kPlanRec + c);
-        st.class_staged[c] = total(kPlanStaged + c);
+        st.class_staged[c] = total((plan.n_work_tiles[c] ? kPlanWorkStaged : kPlanStaged) + c);
         st.class_probes[c] = total(kPlanProbes + c);
         st.n_tiles += st.class_tiles[c];
     }

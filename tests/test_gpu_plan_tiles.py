@@ -1,6 +1,6 @@
 """The tiles that a survey walks under a plan: a cap that a caller chose is
-walked as it is, the default cap is cut finer on small graphs, and the
-statistics report the walked tiles.  Targets of the tiny, small and large class
+walked as it is, the default cap is cut finer on small graphs (but not into
+many times as many tiles), and the statistics report the walked tiles.  Targets of the tiny, small and large class
 with record counts at the edges of a wave (64), of its blocks of records (128,
 192) and of the caps, through every kernel form, against closed forms.  All
 values are integers: the comparison is exact."""
@@ -17,7 +17,8 @@ TIME = 12345
 DEFAULT = (1024, 1024, 16384, 16384)
 BOUNDS = (51, 819, 3276)  # largest d+ of the tiny, small and large class
 LEAST = (16, 32, 512, 512)  # fewest records of the finer cut's cap
-CLAIMERS = (256 * 32 * 8, 256 * 5 * 8, 256 * 4, 256 * 4)
+CLAIMERS = (256 * 32, 256 * 5, 256, 256)
+SHARE = (8, 8, 4, 4)  # tiles for each of them
 
 
 @pytest.fixture(scope="module")
@@ -55,10 +56,16 @@ def expected_tiles(G, caps):
     tiles, staged = [], []
     for k in range(4):
         on = (cls == k) & (cnt > 0)
-        cap = caps[k]
-        if cap == DEFAULT[k]:
-            cap = min(cap, max(LEAST[k], int(cnt[on].sum()) // CLAIMERS[k]))
-        n = np.minimum(cnt[on], np.maximum(-(-cnt[on] // cap), -(-work[on] // (256 * cap))))
+
+        def cut(cap):
+            return np.minimum(cnt[on], np.maximum(-(-cnt[on] // cap), -(-work[on] // (256 * cap))))
+
+        n = cut(caps[k])
+        if caps[k] == DEFAULT[k]:
+            records = int(cnt[on].sum())
+            finer = cut(min(caps[k], max(LEAST[k], records // (SHARE[k] * CLAIMERS[k]))))
+            if finer.sum() <= 4 * n.sum() or 8 * n.sum() < CLAIMERS[k] or (k == 0 and records < 1 << 20):
+                n = finer
         tiles.append(int(n.sum()))
         staged.append(int((n * d[on]).sum()))
     return tiles, staged

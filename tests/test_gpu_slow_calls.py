@@ -54,3 +54,9 @@ def test_few_large_tiles_fill_the_device(T, hubs):
     launched gets some (in blocks of eight tiles half of them got none: twice
     the time of smaller tiles)."""
     assert tiny_ms(T, hubs, 2048) < 1.5 * tiny_ms(T, hubs, 512)
+
+
+def test_hubs_of_leaves_are_not_cut_too_finely(T, hubs):
+    """The default cut of few targets that hold most of the records (cut six
+    times finer it took 1.9 times as long as tiles of 512)."""
+    assert tiny_ms(T, hubs, 1024) < 1.4 * tiny_ms(T, hubs, 512)
