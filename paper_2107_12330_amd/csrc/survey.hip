@@ -115,11 +115,19 @@ constexpr int small_block()
 static_assert(2 * kRing >= (2 * kWave - 1) + 2 * kWave && kRing >= (kWave - 1) + kWave, "hit ring capacity");
 // Waves per SIMD a kernel's registers must leave room for: 8 in the per-wave
 // form of the plain survey (see survey_kernel) and in the count, as many as
-// their LDS lets reside for the 256-thread metadata survey.
+// their LDS lets reside for the 256-thread metadata survey.  The other per-wave
+// forms wait on memory as well: left to itself the compiler takes 108 registers
+// (4 waves) for the extended one, 97 (4) for participation and 79 (6) for the
+// enumeration; at 5, 5 and 7 waves, with up to 7 registers spilled, uniform
+// graphs of 2^22 vertices and 8 edges each took 4.90 instead of 5.77 ms
+// (degree table), 2.79 instead of 3.21 and 4.35 instead of 4.72.
 template <bool WAVE, int BLOCK, bool META, bool ENUM, int FORM>
 constexpr int min_waves()
 {
     if (BLOCK == kSmallBlockWide) return FORM == kFormExt ? 4 : 6;
+    if (WAVE && ENUM) return 7;
+    if (WAVE && FORM != kFormSurvey) return 5;
+    if (BLOCK == 256 && ENUM) return 5;
     if (FORM != kFormSurvey || ENUM) return 1;
     if (WAVE) return 8;
     return BLOCK == 256 ? (META ? 5 : 8) : 1;
