@@ -60,3 +60,20 @@ def test_hubs_of_leaves_are_not_cut_too_finely(T, hubs):
     """The default cut of few targets that hold most of the records (cut six
     times finer it took 1.9 times as long as tiles of 512)."""
     assert tiny_ms(T, hubs, 1024) < 1.4 * tiny_ms(T, hubs, 512)
+
+
+def test_vertex_participation_of_many_vertices_and_few_edges(T):
+    """A pass over the rows for participation, with as many workgroups as the
+    rows ask for (with two, chosen by the edges, it took 38.8 ms, 17 times the
+    graph's build)."""
+    n, m = 1 << 24, 1 << 15
+    gen = T.Generator(device="cuda")
+    gen.manual_seed(5)
+    src, dst = (T.randint(0, n, (m,), generator=gen, device="cuda").int() for _ in range(2))
+    s = T.cuda.current_stream().cuda_stream
+    build = least(T, lambda: tp.build_graph(n, src, dst, stream=s).close())
+    with tp.build_graph(n, src, dst, stream=s) as G:
+        v = T.zeros(n, dtype=T.int64, device="cuda")
+        part = least(T, lambda: tp.tripoll_participation(G.handle, tp.make_spec(), v.data_ptr(), 0, s))
+    print("build %.3f ms, participation %.3f ms" % (build, part), flush=True)
+    assert part < build
