@@ -1357,6 +1357,17 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
                                       per_block);
         TP_CHECK_LAUNCH();
     }
+    // ids out of range refuse the input: where the sort takes longer than a
+    // wait (some 10 us; 2^24 edges: 1.0 ms), before it, else with the counts
+    // that are read after it
+    unsigned long long hc[2];  // bad ids, self-loops
+    auto check_ids = [&] {
+        TP_HIP(hipMemcpyAsync(hc, counters.get(), sizeof(hc), hipMemcpyDeviceToHost, s));
+        TP_HIP(hipStreamSynchronize(s));
+        if (hc[0]) fail(TP_ERR_INVALID, "tripoll_build: " + std::to_string(hc[0]) + " edge endpoints >= n_vertices");
+    };
+    const bool check_first = M >= size_t(1) << 24;
+    if (check_first) check_ids();
     h_src.release();
     h_dst.release();
     h_ts.release();
@@ -1384,10 +1395,9 @@ static void build_impl(const tp_edge_list *el, hipStream_t s, tp_graph **out, co
             TP_HIP(hipMemsetAsync(toff.get(), 0, sizeof(uint64_t), s));
         }
         scan_u64(toff.get(), toff.get(), nt, true, s);
-        unsigned long long hc[2];
-        TP_HIP(hipMemcpyAsync(hc, counters.get(), sizeof(hc), hipMemcpyDeviceToHost, s));
-        m = read_scalar(toff.get() + nt, s);
-        if (hc[0]) fail(TP_ERR_INVALID, "tripoll_build: " + std::to_string(hc[0]) + " edge endpoints >= n_vertices");
+        TP_HIP(hipMemcpyAsync(&m, toff.get() + nt, sizeof(m), hipMemcpyDeviceToHost, s));
+        if (check_first) TP_HIP(hipStreamSynchronize(s));
+        else check_ids();
         g->stats.n_raw_edges = M;
         g->stats.n_self_loops = hc[1];
         if (m) {

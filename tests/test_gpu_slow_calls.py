@@ -77,3 +77,29 @@ def test_vertex_participation_of_many_vertices_and_few_edges(T):
         part = least(T, lambda: tp.tripoll_participation(G.handle, tp.make_spec(), v.data_ptr(), 0, s))
     print("build %.3f ms, participation %.3f ms" % (build, part), flush=True)
     assert part < build
+
+
+def test_large_inputs_are_refused_before_they_are_sorted(T):
+    """An id out of range costs the pass over the edges that finds it (after
+    the sort it took 29% of a build's time, before it 3%)."""
+    n, m = 1 << 20, 1 << 24
+    gen = T.Generator(device="cuda")
+    gen.manual_seed(7)
+    src, dst = (T.randint(0, n, (m,), generator=gen, device="cuda").int() for _ in range(2))
+    bad = dst.clone()
+    bad[m - 1] = n
+    s = T.cuda.current_stream().cuda_stream
+    held = tp.tripoll_live_bytes()
+
+    def refused():
+        with pytest.raises(tp.TripollError) as e:
+            tp.build_graph(n, src, bad, stream=s)
+        assert e.value.status == tp.TP_ERR_INVALID and "1 edge endpoints" in str(e.value)
+
+    build = least(T, lambda: tp.build_graph(n, src, dst, stream=s).close())
+    refuse = least(T, refused)
+    assert tp.tripoll_live_bytes() == held
+    print("build %.3f ms, refused %.3f ms" % (build, refuse), flush=True)
+    assert refuse < 0.12 * build
+    with tp.build_graph(n, src, dst, stream=s) as G:  # and a good input is built after it
+        assert G.stats()["n_raw_edges"] == m
