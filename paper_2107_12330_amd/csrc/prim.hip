@@ -511,7 +511,8 @@ __global__ __launch_bounds__(kSortBlock) void radix_rows(uint64_t *hist, unsigne
 constexpr unsigned kFewBlocks = 64;
 
 // One pass over digit [shift, shift + RB): histograms, their scan, the
-// stable scatter (values travel when vi is set).
+// stable scatter (values travel when vi is set, as they always do with 64-bit
+// keys).
 template <class K, int RB, class S, bool FEW>
 void sort_pass(const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, size_t n, int shift, unsigned nb, size_t tpb,
                uint64_t *hist, hipStream_t s)
@@ -522,10 +523,11 @@ void sort_pass(const K *ki, const uint32_t *vi, K *ko, uint32_t *vo, size_t n, i
         radix_rows<<<1u << RB, kSortBlock, 0, s>>>(hist, nb);
         TP_CHECK_LAUNCH();
     }
-    if (vi)
+    if (sizeof(K) == 8 || vi) {
         radix_downsweep<K, true, RB, S, FEW><<<nb, S::kBlock, 0, s>>>(ki, vi, ko, vo, n, shift, tpb, hist);
-    else
+    } else if constexpr (sizeof(K) == 4) {
         radix_downsweep<K, false, RB, S, FEW><<<nb, S::kBlock, 0, s>>>(ki, nullptr, ko, nullptr, n, shift, tpb, hist);
+    }
     TP_CHECK_LAUNCH();
 }
 
@@ -676,7 +678,10 @@ bool radix_sort(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, size_t
                 int begin_bit)
 {
     if (n <= 1 || bits <= 0) return false;
-    if (sizeof(K) == 8 && n >= kWideKeys) return radix_sort_shape<K, SortWide, false>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
+    if constexpr (sizeof(K) == 8) {
+        if (n >= kWideKeys)
+            return radix_sort_shape<K, SortWide, false>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
+    }
     if (n <= (size_t)kFewBlocks * SortSmall::kTile)
         return radix_sort_shape<K, SortSmall, true>(keys, vals, keys_alt, vals_alt, n, bits, s, begin_bit);
     if (n <= (size_t)kFewBlocks * SortNarrow::kTile)
