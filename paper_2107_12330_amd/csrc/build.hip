@@ -399,8 +399,10 @@ __global__ __launch_bounds__(kCountBlock) void k_degree_count(const uint32_t *v,
 
 // Whether the ends are counted so: ids of 13 to 26 bits, whose parts are at
 // most two LDS ranges (2^28 vertices with 4.2e9 ends have eight, each a reading
-// of the part: the degree phase took 143 ms so, 119 with the sort), and enough
-// ends for each part's counters to be worth clearing and adding up.
+// of the part: the degree phase took 143 ms so, 119 with the sort; 2^27 with
+// 1.07e9 ends have four: 28.5 so, 31.7 with the sort, and 13.2 against 13.3 with
+// 1.3e8), and enough ends for each part's counters to be worth clearing and
+// adding up.
 bool degree_by_count(size_t m, uint32_t n, int nb) { return nb >= 13 && nb <= 26 && m >= (size_t)1 << 20 && m >= n; }
 
 // A bijection of [0, 2^nb): xor-shifts and odd multiplications modulo 2^nb.
@@ -701,7 +703,8 @@ __device__ __forceinline__ uint32_t tiles_of(uint64_t cnt, uint64_t work, uint32
 // the larger two classes) at the plan's cap, its records are cut finer, down to a floor
 // below which a tile's table and claim would outweigh its records.  The
 // claimers are waves for the tiny class and workgroups for the others, as
-// many as 256 compute units hold (32 waves, 5 and 1 workgroups each).  Without
+// many as the plain survey keeps on kPlanUnits compute units (32 waves, 5 and 1
+// workgroups each; the other forms keep fewer).  Without
 // it a small graph waits for the one wave or workgroup that walks its largest
 // target (scale 13: 1024 records on one wave, 247 us of a 380 us survey).
 // 8 tiles against 4: 300-graph batch's tiny class 1.63 against 2.07 ms, 300,007
@@ -709,7 +712,7 @@ __device__ __forceinline__ uint32_t tiles_of(uint64_t cnt, uint64_t work, uint32
 // against 2.63 ms.
 __host__ __device__ inline uint64_t class_claimers(int c)
 {
-    return c == kClassTiny ? 256 * 32 : (c == kClassSmall ? 256 * 5 : 256);
+    return (uint64_t)kPlanUnits * (c == kClassTiny ? 32 : (c == kClassSmall ? 5 : 1));
 }
 
 __device__ __forceinline__ uint32_t work_rec_cap(int c, uint32_t rec_cap, uint64_t class_records)
@@ -754,8 +757,8 @@ __device__ __forceinline__ void piece_records(const uint64_t *fbase, const uint6
     count = pos[fbase[q] + (j + 1) * cnt] - first;
 }
 
-// Records of every class (the work tiles' caps follow from them), and the
-// largest d+; one atomic per block and value.
+// Records of every class (the work tiles' caps follow from them); one atomic
+// per block and value.
 __global__ __launch_bounds__(kB) void k_plan_records(const uint32_t *incnt, const uint64_t *rowptr, uint32_t n,
                                                      unsigned long long *rec /* [classes] */)
 {

@@ -58,6 +58,11 @@ constexpr uint32_t kWorkRecMinTiny = 16;
 constexpr uint32_t kWorkRecMinSmall = 32;
 constexpr uint32_t kWorkRecMinLarge = 512;
 
+// Compute units that the finer cut and the passes of one workgroup each are
+// sized for: an MI355X's.  A heuristic, no limit: on fewer units the tiles are
+// only finer than they need be, and the plan is the same on every partition.
+constexpr uint32_t kPlanUnits = 256;
+
 // Slots of padding after the last oriented edge in the target and time
 // arrays, so that a wave may load 64 consecutive slots from any row start.
 constexpr uint64_t kRowPad = 64;

@@ -2679,7 +2679,8 @@ extern "C" tp_status tripoll_participation(const tp_graph *g, const tp_survey_sp
                 // one workgroup a compute unit, fewer where there are few edges
                 // and few rows for each (2^26 vertices with 2^15 edges: 156 ms
                 // on the two workgroups of their edges, now 3.4)
-                const unsigned blocks = (unsigned)std::min<uint64_t>(256, std::max(g->m / 32768, (uint64_t)g->n / 8192) + 1);
+                const unsigned blocks =
+                    (unsigned)std::min<uint64_t>(kPlanUnits, std::max(g->m / 32768, (uint64_t)g->n / 8192) + 1);
                 k_part_rows<<<blocks, kPartBlock, lds, s>>>(g->rowptr.get(), g->col.get(), g->n, edge, acc.get());
                 TP_CHECK_LAUNCH();
             }
