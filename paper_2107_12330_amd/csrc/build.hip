@@ -724,26 +724,31 @@ __device__ __forceinline__ uint32_t work_rec_cap(int c, uint32_t rec_cap, uint64
     return (uint32_t)min((uint64_t)rec_cap, max((uint64_t)least, want));
 }
 
-// Whether a class is cut finer after all, given its records, its tiles at the
-// plan's cap and the finer ones: not into more than four times as many, where
-// the plan's tiles are as many as an eighth of the claimers.  That is where few
-// targets hold most of the records, hubs of leaves.  Every finer tile fills
-// its target's table again (331,000 records of hubs with d+ of some 700, small
-// class: 477 tiles 63 us, 10,555 tiles 180 us), and since the tiles of a target
-// interleave, each walks the whole range of its rows, which the targets walked
-// at the same time share in cache (10e6 records of hubs with d+ of 17, tiny
-// class, count and survey: 11,250 tiles 515 and 925 us, 67,304 tiles 1012 and
-// 1397).  The tiny class's tables are filled by a wave in one round, and up to
-// 2^20 records its finer tiles are the faster ones (542,000: 128 against 97 us
-// of count and 179 against 110 of survey; 1,376,000: 90 against 151 and 140
-// against 169).  R-MAT graphs are cut into at most 2.8 (tiny) and 4.5 (small)
-// times as many: at 4.2 and 4.5 the small class took 48 and 139 us uncut,
-// 57 and 171 cut.
+// Whether a class is cut finer after all, given its records, its wedge checks,
+// its tiles at the plan's cap and the finer ones: not into more than four times
+// as many, where the plan's tiles are as many as an eighth of the claimers and
+// hold fewer than 2^16 checks each.  That is where few targets hold most of the
+// records, hubs of leaves.  Every finer tile costs a claim (17 ns on one counter
+// for all) and fills its target's table again (331,000 records of hubs with d+
+// of some 700, small class, count: 477 tiles 63 us, 10,555 tiles 180 us), and
+// since the tiles of a target interleave, each walks the whole range of its
+// rows, which the targets walked at the same time share in cache (10e6 records
+// of hubs with d+ of 17, tiny class, count and survey: 11,250 tiles 515 and
+// 925 us, 67,304 tiles 1012 and 1397).  Longer tiles leave a tail that the finer
+// ones fill (complete graph of 1500, small class, survey: 1800 tiles of 177,000
+// checks 870 us, 17,509 tiles 752; 2000 vertices at density 0.3, 46,000 checks:
+// 183 against 211 finer).  The tiny class's tables are filled by a wave in one
+// round, and up to 2^20 records its finer tiles are the faster ones (542,000:
+// 128 against 97 us of count and 179 against 110 of survey; 1,376,000: 90
+// against 151 and 140 against 169).  R-MAT graphs are cut into at most 2.8
+// (tiny) and 5.2 (small) times as many: at 4.2, 4.5 and 5.2 the small class took
+// 47, 141 and 166 us uncut, 53, 169 and 164 cut.
 constexpr uint64_t kFinerMost = 4;
 constexpr uint64_t kFinerTinyRecords = uint64_t(1) << 20;
-bool cut_finer(int c, uint64_t records, uint64_t tiles, uint64_t finer)
+constexpr uint64_t kFinerChecks = uint64_t(1) << 16;
+bool cut_finer(int c, uint64_t records, uint64_t checks, uint64_t tiles, uint64_t finer)
 {
-    return finer <= kFinerMost * tiles || 8 * tiles < class_claimers(c) ||
+    return finer <= kFinerMost * tiles || 8 * tiles < class_claimers(c) || checks >= kFinerChecks * tiles ||
            (c == kClassTiny && records < kFinerTinyRecords);
 }
 
@@ -1208,7 +1213,7 @@ CutPlan cut_plan(const tp_graph *g, const PlanCfg &cfg, hipStream_t s)
         plan.n_tiles[c] = nt;
         plan.tiles[c].reset(std::max<uint64_t>(nt, 1), s);
         // (a finer cut gives no target fewer tiles: as many in all is the same cut)
-        plan.n_work_tiles[c] = nw == nt || !cut_finer(c, total(kPlanRec + c), nt, nw) ? 0 : nw;
+        plan.n_work_tiles[c] = nw == nt || !cut_finer(c, total(kPlanRec + c), total(kPlanProbes + c), nt, nw) ? 0 : nw;
         plan.work_tiles[c].reset(plan.n_work_tiles[c], s);
         out.tiles[c] = nt ? plan.tiles[c].get() : nullptr;
         out.work[c] = plan.work_tiles[c].get();

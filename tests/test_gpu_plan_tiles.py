@@ -64,7 +64,8 @@ def expected_tiles(G, caps):
         if caps[k] == DEFAULT[k]:
             records = int(cnt[on].sum())
             finer = cut(min(caps[k], max(LEAST[k], records // (SHARE[k] * CLAIMERS[k]))))
-            if finer.sum() <= 4 * n.sum() or 8 * n.sum() < CLAIMERS[k] or (k == 0 and records < 1 << 20):
+            if (finer.sum() <= 4 * n.sum() or 8 * n.sum() < CLAIMERS[k] or work[on].sum() >= int(n.sum()) << 16
+                    or (k == 0 and records < 1 << 20)):
                 n = finer
         tiles.append(int(n.sum()))
         staged.append(int((n * d[on]).sum()))
