@@ -513,7 +513,8 @@ tp_status tripoll_survey_batch(const tp_graph *g, const tp_survey_spec *spec, ui
  *   tripoll_launch_replay   enqueues one replay on `stream`; replays on one
  *                           launch must not overlap (they share dev_out)
  *   tripoll_launch_free     releases it (NULL accepted); the graph must
- *                           outlive the launch
+ *                           outlive the launch, and keep its plan: a launch
+ *                           replays the tiles that it was recorded with
  */
 typedef struct tp_launch tp_launch;
 tp_status tripoll_survey_capture(const tp_graph *g, const tp_survey_spec *spec, uint64_t *dev_out,
