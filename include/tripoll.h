@@ -533,8 +533,8 @@ tp_status tripoll_launch_free(tp_launch *launch);
  * than 256 wedge checks per record of cap, is cut into several interleaved
  * tiles).  Under its default cap (1024; 16384 for the large and huge classes)
  * a class with too few records to keep the device busy is cut finer, into
- * about 8 tiles (4) for everything that claims them, unless few targets hold
- * most of its records; any other cap is walked as it is.  The streamed enumeration always walks the plan's own tiles.
+ * about 8 tiles (4) for everything that claims them, fewer where few targets
+ * hold most of its records; any other cap is walked as it is.  The streamed enumeration always walks the plan's own tiles.
  * Results never depend on the plan, only the time does.
  *   tile_records  power of two in [16, 65536]
  */

@@ -674,10 +674,12 @@ __device__ __forceinline__ int class_of(uint64_t dq)
                              : (dq <= kSmallMaxDeg ? kClassSmall : (dq <= kLargeMaxDeg ? kClassLarge : kClassHuge));
 }
 
-// Tile caps of each class: records per tile and wedge checks per tile.
+// Tile caps of each class: records per tile and wedge checks per tile, and the
+// records of its work tiles where they are bounded (bounded_cap; else 0).
 struct TileCaps {
     uint32_t rec[kNumClasses];
     uint64_t work[kNumClasses];
+    uint32_t bound[kNumClasses];
 };
 
 // ceil(a / b), in 32 bits where both fit (a 64-bit division is some 100
@@ -715,41 +717,46 @@ __host__ __device__ inline uint64_t class_claimers(int c)
     return (uint64_t)kPlanUnits * (c == kClassTiny ? 32 : (c == kClassSmall ? 5 : 1));
 }
 
-__device__ __forceinline__ uint32_t work_rec_cap(int c, uint32_t rec_cap, uint64_t class_records)
+__host__ __device__ inline uint32_t work_rec_cap(int c, uint32_t rec_cap, uint64_t class_records)
 {
     const uint64_t share = c == kClassTiny || c == kClassSmall ? 8 : 4;
     const uint64_t claimers = class_claimers(c);
     const uint32_t least = c == kClassTiny ? kWorkRecMinTiny : (c == kClassSmall ? kWorkRecMinSmall : kWorkRecMinLarge);
     const uint64_t want = class_records / (claimers * share);
-    return (uint32_t)min((uint64_t)rec_cap, max((uint64_t)least, want));
+    const uint64_t cap = want > least ? want : least;
+    return cap < rec_cap ? (uint32_t)cap : rec_cap;
 }
 
-// Whether a class is cut finer after all, given its records, its wedge checks,
-// its tiles at the plan's cap and the finer ones: not into more than four times
-// as many, where the plan's tiles are as many as an eighth of the claimers and
-// hold fewer than 2^16 checks each.  That is where few targets hold most of the
+// The cap of a class's work tiles where that rule would cut it into more than
+// four times as many, 0 elsewhere (its records, its wedge checks, its tiles at
+// the plan's cap and the finer ones).  That is where few targets hold most of the
 // records, hubs of leaves.  Every finer tile costs a claim (17 ns on one counter
 // for all) and fills its target's table again (331,000 records of hubs with d+
-// of some 700, small class, count: 477 tiles 63 us, 10,555 tiles 180 us), and
+// of some 700, small class, count: 477 tiles 62 us, 954 59, 10,555 180), and
 // since the tiles of a target interleave, each walks the whole range of its
 // rows, which the targets walked at the same time share in cache (10e6 records
-// of hubs with d+ of 17, tiny class, count and survey: 11,250 tiles 515 and
-// 925 us, 67,304 tiles 1012 and 1397).  Longer tiles leave a tail that the finer
-// ones fill (complete graph of 1500, small class, survey: 1800 tiles of 177,000
-// checks 870 us, 17,509 tiles 752; 2000 vertices at density 0.3, 46,000 checks:
-// 183 against 211 finer).  The tiny class's tables are filled by a wave in one
-// round, and up to 2^20 records its finer tiles are the faster ones (542,000:
-// 128 against 97 us of count and 179 against 110 of survey; 1,376,000: 90
-// against 151 and 140 against 169).  R-MAT graphs are cut into at most 2.8
-// (tiny) and 5.2 (small) times as many: at 4.2, 4.5 and 5.2 the small class took
-// 47, 141 and 166 us uncut, 53, 169 and 164 cut.
+// of hubs with d+ of 17, tiny class, count and survey: 11,250 tiles 516 and
+// 925 us, 21,402 556 and 944, 67,304 1012 and 1397).  So such a class is cut into
+// about twice its tiles, the tiny class into two for every wave at least, which
+// the forms with more work per triangle want (4.1e6 records of 1000 hubs, tiny
+// class, count / survey / extended: 4341 tiles 93 / 197 / 1772 us, 16,341
+// 129 / 259 / 1321, 64,240 172 / 259 / 1415).
+// The full cut stays where the plan's tiles are fewer than an eighth of the
+// claimers; where they hold 2^16 checks and more, whose tail the finer ones fill
+// (complete graph of 1500, small class, survey: 1800 tiles of 177,000 checks
+// 870 us, 17,509 tiles 752; 2000 vertices at density 0.3, 46,000 checks: 183
+// against 211 finer); and in the tiny class, whose tables a wave fills in one
+// round, up to 2^20 records (542,000: 128 us in 1140 tiles, 97 in 34,438).
+// R-MAT graphs are cut into at most 2.8 (tiny) and 5.2 (small) times as many.
 constexpr uint64_t kFinerMost = 4;
 constexpr uint64_t kFinerTinyRecords = uint64_t(1) << 20;
 constexpr uint64_t kFinerChecks = uint64_t(1) << 16;
-bool cut_finer(int c, uint64_t records, uint64_t checks, uint64_t tiles, uint64_t finer)
+uint32_t bounded_cap(int c, uint32_t rec_cap, uint64_t records, uint64_t checks, uint64_t tiles, uint64_t finer)
 {
-    return finer <= kFinerMost * tiles || 8 * tiles < class_claimers(c) || checks >= kFinerChecks * tiles ||
-           (c == kClassTiny && records < kFinerTinyRecords);
+    if (finer <= kFinerMost * tiles || 8 * tiles < class_claimers(c) || checks >= kFinerChecks * tiles) return 0;
+    if (c == kClassTiny && records < kFinerTinyRecords) return 0;
+    const uint64_t want = std::max(2 * tiles, c == kClassTiny ? 2 * class_claimers(c) : 0);
+    return (uint32_t)std::max<uint64_t>(work_rec_cap(c, rec_cap, records), records / want);
 }
 
 // Records of piece j of target q (pieces of huge targets; pos[] is the
@@ -824,7 +831,14 @@ __device__ __forceinline__ void class_caps(const PlanIn &in, int c, uint32_t &rc
         }
     }
     // (a cap that a caller has chosen is walked as it is)
-    frc = rc == default_tile_records(c) ? work_rec_cap(c, rc, in.rec[c]) : rc;
+    frc = rc;
+    if (rc == default_tile_records(c)) {
+        uint32_t bound = in.caps.bound[0];
+#pragma unroll
+        for (int i = 1; i < kNumClasses; ++i)
+            if (i == c) bound = in.caps.bound[i];
+        frc = bound ? bound : work_rec_cap(c, rc, in.rec[c]);
+    }
     fwc = min(wc, kTileWorkPerRecord * (uint64_t)frc);
 }
 
@@ -1189,23 +1203,33 @@ CutPlan cut_plan(const tp_graph *g, const PlanCfg &cfg, hipStream_t s)
             TP_CHECK_LAUNCH();
         }
     }
-    TileCaps caps;
+    TileCaps caps{};
     for (int c = 0; c < kNumClasses; ++c) {
         caps.rec[c] = cfg.tile_records[c];
         caps.work[c] = kTileWorkPerRecord * cfg.tile_records[c];
     }
-    const PlanIn in{cptr.get(), work.get(), g->rowptr.get(), fbase.get(), pos.get(), rec, n, caps};
+    PlanIn in{cptr.get(), work.get(), g->rowptr.get(), fbase.get(), pos.get(), rec, n, caps};
     const unsigned nb = (unsigned)((n + kPlanChunk - 1) / kPlanChunk);
     DArray<uint64_t> sums((size_t)kPlanRows * nb + 1, s), head(kPlanRows + 1, s);
-    k_plan_count<<<nb, kB, 0, s>>>(in, sums.get());
-    TP_CHECK_LAUNCH();
-    scan_u64(sums.get(), sums.get(), (size_t)kPlanRows * nb, true, s);
-    k_plan_heads<<<1, kWave, 0, s>>>(sums.get(), nb, head.get());
-    TP_CHECK_LAUNCH();
     uint64_t first[kPlanRows + 1];
-    TP_HIP(hipMemcpyAsync(first, head.get(), sizeof(first), hipMemcpyDeviceToHost, s));
-    TP_HIP(hipStreamSynchronize(s));
     auto total = [&](int row) { return first[row + 1] - first[row]; };
+    for (bool bounded = false;;) {
+        k_plan_count<<<nb, kB, 0, s>>>(in, sums.get());
+        TP_CHECK_LAUNCH();
+        scan_u64(sums.get(), sums.get(), (size_t)kPlanRows * nb, true, s);
+        k_plan_heads<<<1, kWave, 0, s>>>(sums.get(), nb, head.get());
+        TP_CHECK_LAUNCH();
+        TP_HIP(hipMemcpyAsync(first, head.get(), sizeof(first), hipMemcpyDeviceToHost, s));
+        TP_HIP(hipStreamSynchronize(s));
+        if (bounded) break;
+        // counted again with a bound on the classes that the rule cuts too fine
+        for (int c = 0; c < kNumClasses; ++c) {
+            in.caps.bound[c] = bounded_cap(c, caps.rec[c], total(kPlanRec + c), total(kPlanProbes + c),
+                                           total(kPlanTiles + c), total(kPlanWork + c));
+            bounded = bounded || in.caps.bound[c];
+        }
+        if (!bounded) break;
+    }
     PlanOut out{};
     bool any = false;
     for (int c = 0; c < kNumClasses; ++c) {
@@ -1213,7 +1237,7 @@ CutPlan cut_plan(const tp_graph *g, const PlanCfg &cfg, hipStream_t s)
         plan.n_tiles[c] = nt;
         plan.tiles[c].reset(std::max<uint64_t>(nt, 1), s);
         // (a finer cut gives no target fewer tiles: as many in all is the same cut)
-        plan.n_work_tiles[c] = nw == nt || !cut_finer(c, total(kPlanRec + c), total(kPlanProbes + c), nt, nw) ? 0 : nw;
+        plan.n_work_tiles[c] = nw == nt ? 0 : nw;
         plan.work_tiles[c].reset(plan.n_work_tiles[c], s);
         out.tiles[c] = nt ? plan.tiles[c].get() : nullptr;
         out.work[c] = plan.work_tiles[c].get();

@@ -63,10 +63,12 @@ def expected_tiles(G, caps):
         n = cut(caps[k])
         if caps[k] == DEFAULT[k]:
             records = int(cnt[on].sum())
-            finer = cut(min(caps[k], max(LEAST[k], records // (SHARE[k] * CLAIMERS[k]))))
-            if (finer.sum() <= 4 * n.sum() or 8 * n.sum() < CLAIMERS[k] or work[on].sum() >= int(n.sum()) << 16
+            finest = min(caps[k], max(LEAST[k], records // (SHARE[k] * CLAIMERS[k])))
+            finer = cut(finest)
+            if not (finer.sum() <= 4 * n.sum() or 8 * n.sum() < CLAIMERS[k] or work[on].sum() >= int(n.sum()) << 16
                     or (k == 0 and records < 1 << 20)):
-                n = finer
+                finer = cut(max(finest, records // max(2 * int(n.sum()), 2 * CLAIMERS[k] if k == 0 else 0)))
+            n = finer
         tiles.append(int(n.sum()))
         staged.append(int((n * d[on]).sum()))
     return tiles, staged
@@ -142,3 +144,32 @@ def test_tuner_times_each_cap(T):
         r = tp.tune_dict(tp.tripoll_tune(G.handle, tp.make_spec(), s))
         assert tp.plan_dict(tp.tripoll_get_plan(G.handle)) == r["chosen"]
         assert tp.survey(G, stream=s)["triangles"] == comb(20, 3) + 30000 * comb(20, 2)
+
+
+@pytest.mark.parametrize("hubs,leaves,each", [(1500, 700_000, 4), (1500, 150_000, 4), (400, 60_000, 10)])
+def test_hubs_of_leaves_are_cut_boundedly(T, hubs, leaves, each):
+    """Few targets with most of the records: the finer cut is bounded from 2^20
+    records of the tiny class on, and in the small class."""
+    gen = T.Generator(device="cuda")
+    gen.manual_seed(hubs + leaves)
+    s = T.cuda.current_stream().cuda_stream
+    a = T.randint(0, hubs, (hubs * each,), generator=gen, device="cuda")
+    src = T.cat([a, T.arange(hubs, hubs + leaves, device="cuda").repeat_interleave(each)]).int()
+    dst = T.randint(0, hubs, (src.numel(),), generator=gen, device="cuda").int()
+    if each == 10:  # hubs joined to most others: small targets
+        iu = np.triu_indices(hubs, 1)
+        src = T.cat([src, T.from_numpy(iu[0].astype(np.int32)).cuda()])
+        dst = T.cat([dst, T.from_numpy(iu[1].astype(np.int32)).cuda()])
+    with tp.build_graph(hubs + leaves, src, dst, stream=s) as G:
+        st = G.stats()
+        print(st["class_records"], st["class_tiles"], flush=True)
+        tiles, staged = expected_tiles(G, DEFAULT)
+        assert st["class_tiles"] == tiles and st["class_staged"] == staged
+        ref = tp.survey(G, stream=s, outputs=("count", "close_hist"), strategy=tp.TP_STRAT_GLOBAL_SEARCH)
+        got = tp.survey(G, stream=s, outputs=("count", "close_hist"))
+        assert got["triangles"] == ref["triangles"] and np.array_equal(got["close_hist"], ref["close_hist"])
+        for caps in ((64,) * 4, (65536,) * 4):
+            tp.tripoll_set_plan(G.handle, tp.make_plan((0,) * 4, caps), s)
+            assert expected_tiles(G, caps) == (G.stats()["class_tiles"], G.stats()["class_staged"])
+            again = tp.survey(G, stream=s, outputs=("count", "close_hist"))
+            assert again["triangles"] == ref["triangles"] and np.array_equal(again["close_hist"], ref["close_hist"])
