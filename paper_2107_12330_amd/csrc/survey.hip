@@ -74,6 +74,15 @@ constexpr uint32_t kRing = 128;    // per-wave ring of queued hits: slot|label(p
 constexpr uint32_t kMaxClaimGroup = 8;
 constexpr uint32_t kMaxClaimWave = 4;
 constexpr uint32_t kMaxClaimBatch = 2;
+// In a batch of small graphs the extended forms claim 8: a wave merges the some
+// 2000 to 8000 words of its counters at every change of graph, and of a block of
+// 16 tiles its workgroup's four waves each walk and merge the same graphs
+// (20,000 graphs of 40 vertices, Algorithm 3's bins, degree and open/close
+// tables: 2.89 ms with claims of 2, 2.53 with 8; 5000 of 300 vertices 8.98 and
+// 7.93; 200 R-MAT-like ones of 2^14, some 5000 tiles each, degree table: 8.87
+// and 11.6).
+constexpr uint32_t kMaxClaimExtSmall = 8;
+constexpr uint64_t kExtSmallTiles = 512;  // per graph
 // The tiles of a batch's launch are cut into kClaimSegs contiguous segments,
 // one per XCD, each with its own claim counter.  Workgroups are dispatched to
 // the 8 XCDs round robin, so workgroup b starts on segment b % 8: the waves of
@@ -218,6 +227,7 @@ struct SurveyParams {
     uint32_t claim_few;       // per-wave form: so few tiles that they are dealt out to the workgroups
     uint32_t claim_seg_log;   // log2 of the claim segments (0 or 3)
     uint32_t clear_claims;    // host: clear the claim counters before the launch
+    uint32_t n_graphs;        // host: graphs of a batch
     // single-graph surveys: class c counts its triangles at class_tri[c]
     unsigned long long *class_tri;
 };
@@ -1817,6 +1827,7 @@ void launch_kernel(const SurveyParams &P, const LdsLayout &L, hipStream_t s, int
     SurveyParams Q = P;
     const uint64_t units = fit * groups;
     uint32_t claim = P.rank_gid ? kMaxClaimBatch : (WAVE ? kMaxClaimWave : kMaxClaimGroup);
+    if (FORM == kFormExt && P.rank_gid && P.n_tiles < kExtSmallTiles * P.n_graphs) claim = kMaxClaimExtSmall;
     while (claim > 1 && Q.n_tiles < (uint64_t)claim * units * 8) claim >>= 1;
     Q.claim = claim;
     Q.claim_seg_log = P.rank_gid ? 3u : 0u;  // segments per XCD for batches (kClaimSegs)
@@ -2164,6 +2175,7 @@ void survey_batch_enqueue(const tp_graph *g, const tp_survey_spec *sp, unsigned 
     TP_CHECK_LAUNCH();
     SurveyParams P = make_params(g, sp, dev_out, dev_out + (total - kClaimWords));
     P.rank_gid = g->n_graphs ? g->rank_gid.get() : nullptr;
+    P.n_graphs = g->n_graphs;
     P.g_stride = words;
     P.o_tri = TP_BW_TRIANGLES;
     P.o_spread = TP_BW_SPREAD;
